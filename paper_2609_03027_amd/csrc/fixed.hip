@@ -4,8 +4,8 @@
 // radix-2 decimation-in-frequency FFT in 16-bit fixed point with a scaling
 // bit per stage, round-half-up and saturation between stages (Sec. 3: the
 // FFT core takes different scaling schemes).  The Eq. 2 products of the
-// integer sky values are summed in FP64, exact for integers below 2^53, so
-// every time slice's sums are exact and their total does not depend on the
+// integer sky values are summed exactly in 64-bit integers, each time slice's
+// sums leave as FP64 (exact below 2^53), and their total does not depend on the
 // order; one reduce scales it back to image units and adds it to the FP32
 // accumulator.
 //
@@ -28,60 +28,143 @@ namespace epic {
 namespace {
 constexpr int FN = 64, FT = 512, FROW = 65;
 
-__device__ __forceinline__ int rsh(int x, int k) { return (x + ((1 << k) >> 1)) >> k; }
-__device__ __forceinline__ int sat16(int x) { return min(max(x, -32768), 32767); }
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 
-struct CI {
-    int r, i;
-};
-
-// Grid cell: two feeds of 16-bit real/imaginary pairs, (re & 0xffff) | im << 16.
+// A complex 16-bit value stays one register (re & 0xffff) | im << 16 from the
+// stage to the products: sums and differences are packed 16-bit operations,
+// complex products two-element dot products with an int32 accumulator.
 __device__ __forceinline__ uint32_t pack16(int r, int i) {
     return ((uint32_t)r & 0xffffu) | ((uint32_t)i << 16);
 }
-__device__ __forceinline__ CI unpack16(uint32_t v) {
-    return CI{(int)(v << 16) >> 16, (int)v >> 16};
+__device__ __forceinline__ s16x2 pk(uint32_t v) { return __builtin_bit_cast(s16x2, v); }
+__device__ __forceinline__ uint32_t un(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+// c + a.lo b.lo + a.hi b.hi, modulo 2^32
+__device__ __forceinline__ int dot2(uint32_t a, uint32_t b, int c) {
+    return __builtin_amdgcn_sdot2(pk(a), pk(b), c, false);
+}
+// The same where the result fits int32: the saturating form takes its third
+// operand from any register, the plain one overwrites it (a copy per use).
+__device__ __forceinline__ int dot2_fit(uint32_t a, uint32_t b, int c) {
+    return __builtin_amdgcn_sdot2(pk(a), pk(b), c, true);
+}
+// (sat16(r), sat16(i))
+__device__ __forceinline__ uint32_t sat_pack(int r, int i) {
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_i16(r, i));
+}
+__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) {
+    return un(__builtin_elementwise_add_sat(pk(a), pk(b)));
+}
+__device__ __forceinline__ uint32_t sub_sat(uint32_t a, uint32_t b) {
+    return un(__builtin_elementwise_sub_sat(pk(a), pk(b)));
+}
+__device__ __forceinline__ uint32_t half_floor(uint32_t a) { return un(pk(a) >> (short)1); }
+// (im of a, re of a): the halves swapped
+__device__ __forceinline__ uint32_t swap16(uint32_t a) { return __builtin_amdgcn_alignbit(a, a, 16); }
+
+// sat16(rsh(a + c, SH)) per half.  Halving: a + c = 2 (a | c) - (a ^ c), so
+// floor((a + c + 1) / 2) = (a | c) - floor((a ^ c) / 2), always in range.
+template <bool SH> __device__ __forceinline__ uint32_t sum16(uint32_t a, uint32_t c) {
+    if (!SH) return add_sat(a, c);
+    return un(pk(a | c) - pk(half_floor(a ^ c)));
+}
+// sat16(rsh(a - c, SH)) per half.  Halving: a - c + 1 = 2 (a & ~c) - (a ^ c) + 1,
+// so floor((a - c + 1) / 2) = (a & ~c) - floor((a ^ c) / 2), which reaches
+// 32768 (a = 32767, c = -32768): the last subtraction saturates.
+template <bool SH> __device__ __forceinline__ uint32_t dif16(uint32_t a, uint32_t c) {
+    if (!SH) return sub_sat(a, c);
+    return sub_sat(a & ~c, half_floor(a ^ c));
 }
 
-// One radix-2 DIF butterfly of the definition above.  |a - c| < 2^16 and
-// |w| <= 2^14, so both 24-bit products and their sum stay inside int32.
-__device__ __forceinline__ void bfly(CI &a, CI &c, int2 w, int ts, int sh) {
-    const int ur = a.r + c.r, ui = a.i + c.i;
-    const int dr = a.r - c.r, di = a.i - c.i;
-    const int vr = __mul24(dr, w.x) - __mul24(di, w.y);
-    const int vi = __mul24(dr, w.y) + __mul24(di, w.x);
-    a.r = sat16(rsh(ur, sh));
-    a.i = sat16(rsh(ui, sh));
-    c.r = sat16(rsh(vr, ts + sh));
-    c.i = sat16(rsh(vi, ts + sh));
+// A twiddle as the four dot-product operands (wr, -wi), (-wr, wi), (wi, wr),
+// (-wi, -wr): |w| <= 2^14, so every half is exact.
+struct TwW {
+    uint32_t p, pn, q, qn;
+};
+__device__ __forceinline__ TwW tw_operands(int2 w) {
+    return TwW{pack16(w.x, -w.y), pack16(-w.x, w.y), pack16(w.y, w.x), pack16(-w.y, -w.x)};
+}
+
+// One radix-2 DIF butterfly of the definition above, t = ts + SH, rnd =
+// 2^(t-1).  The product (a - c) w is a w + c (-w); with |wr| + |wi| <=
+// sqrt(2) 2^14 + 1, a w + rnd stays below 2^30 and the whole below 2^31.
+template <bool SH>
+__device__ __forceinline__ void bfly(uint32_t &a, uint32_t &c, const TwW &w, int t, int rnd) {
+    const int vr = dot2(c, w.pn, dot2_fit(a, w.p, rnd));
+    const int vi = dot2(c, w.qn, dot2_fit(a, w.q, rnd));
+    a = sum16<SH>(a, c);
+    c = sat_pack(vr >> t, vi >> t);
+}
+// w = 2^ts: rsh((a - c) 2^ts, ts + sh) = rsh(a - c, sh)
+template <bool SH> __device__ __forceinline__ void bfly_1(uint32_t &a, uint32_t &c) {
+    const uint32_t d = dif16<SH>(a, c);
+    a = sum16<SH>(a, c);
+    c = d;
+}
+// w = i 2^ts: (re, im) = (c.im - a.im, a.re - c.re), rounded the same way
+template <bool SH> __device__ __forceinline__ void bfly_i(uint32_t &a, uint32_t &c) {
+    const uint32_t d = dif16<SH>(__builtin_amdgcn_alignbit(a, c, 16), __builtin_amdgcn_alignbit(c, a, 16));
+    a = sum16<SH>(a, c);
+    c = d;
 }
 
 // Stages 0-2 of an axis on the 8 elements j + 8 m (m = 0..7) of a line:
 // stage 0 pairs (m, m+4) with twiddle index j + 8 m; stage 1 pairs
 // (m, m+2), m in {0, 1, 4, 5}, index 2 (j + 8 (m & 1)); stage 2 pairs
 // (m, m+1), m even, index 4 j.  wa[0..3] = w_{j+8m}, wa[4..5] =
-// w_{2(j+8b)}, wa[6] = w_{4j}.
-__device__ __forceinline__ void stages_012(CI *v, const int2 *wa, int ts, int s0, int s1, int s2) {
+// w_{2(j+8b)}, wa[6] = w_{4j}.  Every stage exists with and without halving;
+// the scaling bits are uniform, so a stage costs one scalar branch.
+template <int ST, bool SH>
+__device__ __forceinline__ void stage_a(uint32_t *v, const TwW *wa, int ts, const int *rn) {
+    const int t = ts + (SH ? 1 : 0), rnd = rn[SH ? 1 : 0];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) bfly(v[m], v[m + 4], wa[m], ts, s0);
-#pragma unroll
-    for (int m = 0; m < 8; ++m)
-        if ((m & 2) == 0) bfly(v[m], v[m + 2], wa[4 + (m & 1)], ts, s1);
-#pragma unroll
-    for (int m = 0; m < 8; m += 2) bfly(v[m], v[m + 1], wa[6], ts, s2);
+    for (int m = 0; m < 8; ++m) {
+        if (ST == 0 && m < 4) bfly<SH>(v[m], v[m + 4], wa[m], t, rnd);
+        if (ST == 1 && (m & 2) == 0) bfly<SH>(v[m], v[m + 2], wa[4 + (m & 1)], t, rnd);
+        if (ST == 2 && (m & 1) == 0) bfly<SH>(v[m], v[m + 1], wa[6], t, rnd);
+    }
 }
-
 // Stages 3-5 of an axis on the 8 elements 8 q + m: stage 3 pairs (m, m+4)
 // with index 8 m; stage 4 pairs (m, m+2), m in {0, 1, 4, 5}, index
-// 16 (m & 1); stage 5 pairs (m, m+1), index 0.  wb[k] = w_{8k}.
-__device__ __forceinline__ void stages_345(CI *v, const int2 *wb, int ts, int s3, int s4, int s5) {
+// 16 (m & 1); stage 5 pairs (m, m+1), index 0.  wb = w_8, w_24.
+template <int ST, bool SH>
+__device__ __forceinline__ void stage_b(uint32_t *v, const TwW *wb, int ts, const int *rn) {
+    const int t = ts + (SH ? 1 : 0), rnd = rn[SH ? 1 : 0];
+    if (ST == 3) {
+        bfly_1<SH>(v[0], v[4]);
+        bfly<SH>(v[1], v[5], wb[0], t, rnd);
+        bfly_i<SH>(v[2], v[6]);
+        bfly<SH>(v[3], v[7], wb[1], t, rnd);
+    }
 #pragma unroll
-    for (int m = 0; m < 4; ++m) bfly(v[m], v[m + 4], wb[m], ts, s3);
-#pragma unroll
-    for (int m = 0; m < 8; ++m)
-        if ((m & 2) == 0) bfly(v[m], v[m + 2], wb[2 * (m & 1)], ts, s4);
-#pragma unroll
-    for (int m = 0; m < 8; m += 2) bfly(v[m], v[m + 1], wb[0], ts, s5);
+    for (int m = 0; m < 8; ++m) {
+        if (ST == 4 && (m & 3) == 0) bfly_1<SH>(v[m], v[m + 2]);
+        if (ST == 4 && (m & 3) == 1) bfly_i<SH>(v[m], v[m + 2]);
+        if (ST == 5 && (m & 1) == 0) bfly_1<SH>(v[m], v[m + 1]);
+    }
+}
+// Stages s0 .. s0 + 2 of the mask on both feeds.  ALL: every bit is set.
+template <int P, bool ALL>
+__device__ __forceinline__ void stages_012(uint32_t *x, uint32_t *y, const TwW *wa, int ts,
+                                           const int *rn, uint32_t mask) {
+#define EPIC_STAGE(F, ST, W)                       \
+    if (ALL || ((mask >> ST) & 1u)) {              \
+        F<ST, true>(x, W, ts, rn);                 \
+        if (P == 2) F<ST, true>(y, W, ts, rn);     \
+    } else {                                       \
+        F<ST, false>(x, W, ts, rn);                \
+        if (P == 2) F<ST, false>(y, W, ts, rn);    \
+    }
+    EPIC_STAGE(stage_a, 0, wa)
+    EPIC_STAGE(stage_a, 1, wa)
+    EPIC_STAGE(stage_a, 2, wa)
+}
+template <int P, bool ALL>
+__device__ __forceinline__ void stages_345(uint32_t *x, uint32_t *y, const TwW *wb, int ts,
+                                           const int *rn, uint32_t mask) {
+    EPIC_STAGE(stage_b, 3, wb)
+    EPIC_STAGE(stage_b, 4, wb)
+    EPIC_STAGE(stage_b, 5, wb)
+#undef EPIC_STAGE
 }
 
 __device__ __forceinline__ int brev6(int p) { return (int)(__brev((unsigned)p) >> 26); }
@@ -91,20 +174,38 @@ __device__ __forceinline__ int2 uni2(int2 v) {
 }
 }  // namespace
 
-// One workgroup per (channel, time slice); 512 threads; thread j = tid / 64
-// is the wave index, so pass-A twiddles are wave-uniform.  Gather entries as
-// in the FP32 fused path, with integer weights conj(q) (-1)^(jx+jy) in
-// place of the float ones.  part: double [slice][item][P == 2 ? 4 : 1][4096]
-// sums in natural pixel order; slices with no samples write zeros.
-template <int P>
-__global__ __launch_bounds__(FT) void k_fixed64(const FusedItem *__restrict__ items, int n_items,
-                                                const uint4 *__restrict__ entries,
-                                                const uint8_t *__restrict__ volt,
-                                                int64_t volt_t_stride, int A, int n_time,
-                                                int t_per_slice, const int2 *__restrict__ tw,
-                                                int ts, uint32_t mask, int sg,
-                                                double *__restrict__ part, int vb) {
+// One workgroup per (channel, time slice); 512 threads; j = tid / 64 is the
+// wave index, so pass-A twiddles are wave-uniform.  Gather entry (uint2): x =
+// element | cell << 14 | last-tap-of-cell << 31, y = the conjugate weight
+// q' = conj(q) (-1)^(jx+jy) as the dot-product operand (q'r, -q'i).  Every
+// entry stores the running sum, so the loop has no per-lane branches: a cell's
+// last tap to the cell, the others to column 64, which no pass reads.
+// The first 2 EB entries of a lane stay in registers for the whole sample loop
+// (they are the same every sample; 256 elements with a
+// 3 x 3 kernel fill five, and no entries are read then), and each sample's
+// voltages are loaded during the sample before.  The Eq. 2 products are formed
+// as unsigned 32-bit integers (the cross products with a bias of 2^31 - 1, so
+// that x = y = -32768 - 32768 i still fits) and summed in 64 bits.  With
+// `autos` (A <= 512) the self-term sums are added here.
+// part: double [slice][item][P == 2 ? 4 : 1][4096] sums in natural pixel
+// order; slices with no samples write zeros.
+//
+// Bound: vector issue.  A thread and sample takes about 12 instructions per
+// butterfly with a general twiddle (4 packed for the sum, 4 dot products, 2
+// shifts and 1 saturating pack for the product) and 6 with a unit one, about
+// 1200 in all.  64 channels, 256 elements, K = 2, 8+8 bits, 1000 samples: 1.17 ms
+// with the reduce, 2.05 ms with every part unpacked to 32 bits, FP64 product
+// sums, entries read from L2 one by one and a separate self-term pass.
+//
+// ALL: every stage halves (the default mask), so the stages need no branches.
+template <int P, bool ALL>
+__global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4))) void k_fixed64(
+    const FusedItem *__restrict__ items, int n_items, const uint2 *__restrict__ entries,
+    const uint8_t *__restrict__ volt, int64_t volt_t_stride, int A, int n_time, int t_per_slice,
+    const int2 *__restrict__ tw, int ts, uint32_t mask, int sg, double *__restrict__ part, int vb,
+    int32_t *__restrict__ autos) {
     constexpr int NPROD = P == 2 ? 4 : 1;
+    constexpr int EB = 3;
     extern __shared__ uint2 smem[];
     uint2 *grid = smem;                  // [64][65] cells
     uint2 *stage = smem + FN * FROW;     // [A] staged voltages
@@ -114,146 +215,208 @@ __global__ __launch_bounds__(FT) void k_fixed64(const FusedItem *__restrict__ it
     const int line = tid & 63;
     const int j = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    int2 wa[7], wb[4];
+    TwW wa[7], wb[2];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) wa[m] = uni2(tw[j + 8 * m]);
-    wa[4] = uni2(tw[2 * j]);
-    wa[5] = uni2(tw[2 * (j + 8)]);
-    wa[6] = uni2(tw[4 * j]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wb[k] = tw[8 * k];
-    int sh[12];
-#pragma unroll
-    for (int s = 0; s < 12; ++s) sh[s] = (mask >> s) & 1u;
+    for (int m = 0; m < 4; ++m) wa[m] = tw_operands(uni2(tw[j + 8 * m]));
+    wa[4] = tw_operands(uni2(tw[2 * j]));
+    wa[5] = tw_operands(uni2(tw[2 * (j + 8)]));
+    wa[6] = tw_operands(uni2(tw[4 * j]));
+    wb[0] = tw_operands(uni2(tw[8]));
+    wb[1] = tw_operands(uni2(tw[24]));
 
     for (int i = tid; i < FN * FROW; i += FT) grid[i] = make_uint2(0u, 0u);
-    double acc[8][NPROD];
+    uint32_t acc[8][NPROD], acch[8][NPROD];      // 64-bit sums, low and high halves
 #pragma unroll
     for (int m = 0; m < 8; ++m)
 #pragma unroll
-        for (int q = 0; q < NPROD; ++q) acc[m][q] = 0.0;
+        for (int q = 0; q < NPROD; ++q) acc[m][q] = acch[m][q] = 0u;
 
     const int t0 = slice * t_per_slice;
     const int t1 = min(n_time, t0 + t_per_slice);
     const uint8_t *vbase = volt + (int64_t)it.c * P * A * vb;
-    const uint4 *ent = entries + it.entry_off + tid;
+    const uint2 *ent = entries + it.entry_off + tid;
+    const int n_iter = it.n_iter;
+    auto entry = [&](int k) {
+        // past the list: no weight, not a cell's last tap, the unread column
+        return k < n_iter ? ent[(int64_t)k * FT] : make_uint2((uint32_t)FN << 14, 0u);
+    };
+    uint2 held[2 * EB];
+#pragma unroll
+    for (int k = 0; k < 2 * EB; ++k) held[k] = entry(k);
+    // this sample's voltages of element tid, loaded one sample ahead
+    uint32_t rx = 0u, ry = 0u;
+    if (tid < A && t0 < t1) {
+        const uint8_t *v0 = vbase + (int64_t)t0 * volt_t_stride;
+        rx = volt_raw(v0, tid, vb);
+        ry = P == 2 ? volt_raw(v0, A + tid, vb) : 0u;
+    }
+    int sa[NPROD];
+#pragma unroll
+    for (int q = 0; q < NPROD; ++q) sa[q] = 0;
+    const int half = (1 << sg) >> 1;
+    // rounding terms without and with halving; kept in vector registers, since
+    // a dot product takes one scalar operand (the twiddle)
+    int rn[2] = {1 << (ts - 1), 1 << ts};
+    asm volatile("" : "+v"(rn[0]), "+v"(rn[1]));
     for (int t = t0; t < t1; ++t) {
         const uint8_t *vt = vbase + (int64_t)t * volt_t_stride;
-        for (int a = tid; a < A; a += FT) {
+        if (tid < A) {
+            const int2 x = volt_dec(rx, vb);
+            const int2 y = P == 2 ? volt_dec(ry, vb) : make_int2(0, 0);
+            stage[tid] = make_uint2(pack16(x.x, x.y), pack16(y.x, y.y));
+            if (autos) {
+                sa[0] += x.x * x.x + x.y * x.y;
+                if (P == 2) {
+                    sa[1] += y.x * y.x + y.y * y.y;
+                    sa[2] += x.x * y.x + x.y * y.y;
+                    sa[3] += x.y * y.x - x.x * y.y;
+                }
+            }
+        }
+        for (int a = tid + FT; a < A; a += FT) {
             const int2 x = volt_at(vt, a, vb);
             const int2 y = P == 2 ? volt_at(vt, A + a, vb) : make_int2(0, 0);
             stage[a] = make_uint2(pack16(x.x, x.y), pack16(y.x, y.y));
         }
         __syncthreads();
+        if (t + 1 < t1 && tid < A) {
+            rx = volt_raw(vt + volt_t_stride, tid, vb);
+            ry = P == 2 ? volt_raw(vt + volt_t_stride, A + tid, vb) : 0u;
+        }
         {
-            int sxr = 0, sxi = 0, syr = 0, syi = 0;
-            for (int k = 0; k < it.n_iter; ++k) {
-                const uint4 e = ent[(int64_t)k * FT];
-                const uint2 v = stage[e.x & 0xFFFFu];
-                const CI ex = unpack16(v.x), ey = unpack16(v.y);
-                const int wr = (int)e.z, wi = (int)e.w;
-                sxr += __mul24(wr, ex.r) - __mul24(wi, ex.i);
-                sxi += __mul24(wr, ex.i) + __mul24(wi, ex.r);
-                if (P == 2) {
-                    syr += __mul24(wr, ey.r) - __mul24(wi, ey.i);
-                    syi += __mul24(wr, ey.i) + __mul24(wi, ey.r);
+            int sxr = half, sxi = half, syr = half, syi = half;
+            uint2 e[EB];
+            for (int k0 = 0; k0 < n_iter; k0 += EB) {
+                if (k0 < 2 * EB) {
+#pragma unroll
+                    for (int k = 0; k < EB; ++k) {
+                        // decoded per sample: hoisted out of the loop the
+                        // addresses and swapped operands would take three
+                        // registers an entry
+                        e[k] = k0 ? held[EB + k] : held[k];
+                        asm volatile("" : "+v"(e[k].x), "+v"(e[k].y));
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < EB; ++k) e[k] = entry(k0 + k);
                 }
-                if (e.x >> 31) {
-                    grid[e.y] = make_uint2(pack16(sat16(rsh(sxr, sg)), sat16(rsh(sxi, sg))),
-                                           pack16(sat16(rsh(syr, sg)), sat16(rsh(syi, sg))));
-                    sxr = sxi = syr = syi = 0;
+                uint2 v[EB];
+#pragma unroll
+                for (int k = 0; k < EB; ++k) v[k] = stage[e[k].x & 0x3FFFu];
+#pragma unroll
+                for (int k = 0; k < EB; ++k) {
+                    const uint32_t wp = e[k].y;                             // (q'r, -q'i)
+                    const uint32_t wq = un(pk(swap16(wp)) * s16x2{-1, 1});  // (q'i, q'r)
+                    sxr = dot2(v[k].x, wp, sxr);
+                    sxi = dot2(v[k].x, wq, sxi);
+                    if (P == 2) {
+                        syr = dot2(v[k].y, wp, syr);
+                        syi = dot2(v[k].y, wq, syi);
+                    }
+                    grid[(e[k].x >> 14) & 0x1FFFu] = make_uint2(
+                        sat_pack(sxr >> sg, sxi >> sg), P == 2 ? sat_pack(syr >> sg, syi >> sg) : 0u);
+                    const bool last = (e[k].x >> 31) != 0u;
+                    sxr = last ? half : sxr;
+                    sxi = last ? half : sxi;
+                    syr = last ? half : syr;
+                    syi = last ? half : syi;
                 }
             }
         }
         __syncthreads();
         // rows (along x): stages 0-2 on elements j + 8 m of row `line`
         {
-            CI vx[8], vy[8];
+            uint32_t vx[8], vy[8];
             const int base = line * FROW + j;
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
                 const uint2 g = grid[base + 8 * m];
-                vx[m] = unpack16(g.x);
-                vy[m] = unpack16(g.y);
+                vx[m] = g.x;
+                vy[m] = g.y;
             }
-            stages_012(vx, wa, ts, sh[0], sh[1], sh[2]);
-            if (P == 2) stages_012(vy, wa, ts, sh[0], sh[1], sh[2]);
+            stages_012<P, ALL>(vx, vy, wa, ts, rn, mask);
 #pragma unroll
-            for (int m = 0; m < 8; ++m)
-                grid[base + 8 * m] = make_uint2(pack16(vx[m].r, vx[m].i), pack16(vy[m].r, vy[m].i));
+            for (int m = 0; m < 8; ++m) grid[base + 8 * m] = make_uint2(vx[m], vy[m]);
         }
         __syncthreads();
         // rows: stages 3-5 on elements 8 j + m
         {
-            CI vx[8], vy[8];
+            uint32_t vx[8], vy[8];
             const int base = line * FROW + 8 * j;
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
                 const uint2 g = grid[base + m];
-                vx[m] = unpack16(g.x);
-                vy[m] = unpack16(g.y);
+                vx[m] = g.x;
+                vy[m] = g.y;
             }
-            stages_345(vx, wb, ts, sh[3], sh[4], sh[5]);
-            if (P == 2) stages_345(vy, wb, ts, sh[3], sh[4], sh[5]);
+            stages_345<P, ALL>(vx, vy, wb, ts, rn, mask);
 #pragma unroll
-            for (int m = 0; m < 8; ++m)
-                grid[base + m] = make_uint2(pack16(vx[m].r, vx[m].i), pack16(vy[m].r, vy[m].i));
+            for (int m = 0; m < 8; ++m) grid[base + m] = make_uint2(vx[m], vy[m]);
         }
         __syncthreads();
         // columns (along y): stages 0-2 on rows j + 8 m of column `line`
         {
-            CI vx[8], vy[8];
+            uint32_t vx[8], vy[8];
             const int base = j * FROW + line;
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
                 const uint2 g = grid[base + 8 * m * FROW];
-                vx[m] = unpack16(g.x);
-                vy[m] = unpack16(g.y);
+                vx[m] = g.x;
+                vy[m] = g.y;
             }
-            stages_012(vx, wa, ts, sh[6], sh[7], sh[8]);
-            if (P == 2) stages_012(vy, wa, ts, sh[6], sh[7], sh[8]);
+            stages_012<P, ALL>(vx, vy, wa, ts, rn, mask >> 6);
 #pragma unroll
-            for (int m = 0; m < 8; ++m)
-                grid[base + 8 * m * FROW] =
-                    make_uint2(pack16(vx[m].r, vx[m].i), pack16(vy[m].r, vy[m].i));
+            for (int m = 0; m < 8; ++m) grid[base + 8 * m * FROW] = make_uint2(vx[m], vy[m]);
         }
         __syncthreads();
         // columns: stages 3-5 on rows 8 j + m, then the Eq. 2 products; the
         // grid is left zeroed for the next gather (the staging barrier of
         // the next sample orders these writes before it)
         {
-            CI vx[8], vy[8];
+            uint32_t vx[8], vy[8];
             const int base = 8 * j * FROW + line;
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
                 const uint2 g = grid[base + m * FROW];
-                vx[m] = unpack16(g.x);
-                vy[m] = unpack16(g.y);
+                vx[m] = g.x;
+                vy[m] = g.y;
                 grid[base + m * FROW] = make_uint2(0u, 0u);
             }
-            stages_345(vx, wb, ts, sh[9], sh[10], sh[11]);
-            if (P == 2) stages_345(vy, wb, ts, sh[9], sh[10], sh[11]);
+            stages_345<P, ALL>(vx, vy, wb, ts, rn, mask >> 6);
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
-                const double xr = vx[m].r, xi = vx[m].i;
-                acc[m][0] += xr * xr + xi * xi;
+                const uint32_t x = vx[m], y = vy[m];
+                uint32_t pr[4];
+                pr[0] = (uint32_t)dot2(x, x, 0);
                 if (P == 2) {
-                    const double yr = vy[m].r, yi = vy[m].i;
-                    acc[m][1] += yr * yr + yi * yi;
-                    acc[m][2] += xr * yr + xi * yi;
-                    acc[m][3] += xi * yr - xr * yi;
+                    pr[1] = (uint32_t)dot2(y, y, 0);
+                    pr[2] = (uint32_t)dot2(x, y, 0x7fffffff);
+                    // xi yr - xr yi = xi yr + xr (~yi + 1)
+                    pr[3] = (uint32_t)dot2(swap16(x), y ^ 0xffff0000u,
+                                           ((int)(x << 16) >> 16) + 0x7fffffff);
                 }
+#pragma unroll
+                for (int q = 0; q < NPROD; ++q)
+                    acch[m][q] += __builtin_add_overflow(acc[m][q], pr[q], &acc[m][q]);
             }
         }
     }
     // position (8 j + m, line) holds frequency (brev(8 j + m), brev(line))
     double *dst = part + ((int64_t)slice * n_items + item) * NPROD * FN * FN;
     const int kx = brev6(line);
+    const int64_t bias = (int64_t)max(0, t1 - t0) * 0x7fffffff;
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
         const int ky = brev6(8 * j + m);
 #pragma unroll
-        for (int q = 0; q < NPROD; ++q) dst[(int64_t)q * FN * FN + ky * FN + kx] = acc[m][q];
+        for (int q = 0; q < NPROD; ++q)
+            dst[(int64_t)q * FN * FN + ky * FN + kx] =
+                (double)((int64_t)(((uint64_t)acch[m][q] << 32) | acc[m][q]) - (q >= 2 ? bias : 0));
+    }
+    if (autos && tid < A) {
+        int32_t *d = autos + ((int64_t)it.c * A + tid) * NPROD;
+#pragma unroll
+        for (int q = 0; q < NPROD; ++q) atomicAdd(d + q, sa[q]);
     }
 }
 
@@ -308,8 +471,9 @@ epic_status fixed_build(epic_plan p, const std::vector<int> &j0, const std::vect
                     GatherTap tp{};
                     tp.cell = jy * FROW + jx;
                     tp.ant = a;
-                    tp.wr = __builtin_bit_cast(float, sg * qr);    // conj(q) (-1)^(jx+jy)
-                    tp.wi = __builtin_bit_cast(float, -sg * qi);
+                    // conj(q) (-1)^(jx+jy) as the operand (re, -im)
+                    tp.wr = __builtin_bit_cast(float, ((uint32_t)(sg * qr) & 0xffffu) |
+                                                          ((uint32_t)(sg * qi) << 16));
                     taps.push_back(tp);
                     bound[jy * FN + jx] += (int64_t)(std::abs(qr) + std::abs(qi)) * vmax;
                 }
@@ -351,13 +515,19 @@ epic_status fixed_build(epic_plan p, const std::vector<int> &j0, const std::vect
     F.slices = S;
     F.part_bytes = per_slice * S;
     F.n_items = C;
+    // {element | last << 31, cell, operand} -> the kernel's 8-byte entries
+    std::vector<uint2> packed(all.size());
+    for (size_t i = 0; i < all.size(); ++i) {
+        const uint32_t cell = (all[i].x >> 31) ? all[i].y : (uint32_t)(i % FN) * FROW + FN;
+        packed[i] = make_uint2((all[i].x & 0x80003FFFu) | (cell << 14), all[i].z);
+    }
     epic_status st;
     if ((st = F.items.alloc(sizeof(FusedItem) * items.size()))) return st;
-    if ((st = F.entries.alloc(sizeof(uint4) * all.size()))) return st;
+    if ((st = F.entries.alloc(sizeof(uint2) * packed.size()))) return st;
     if ((st = F.tw.alloc(sizeof(int2) * tw.size()))) return st;
     EPIC_HIP(hipMemcpyAsync(F.items.p, items.data(), sizeof(FusedItem) * items.size(),
                             hipMemcpyHostToDevice, s));
-    EPIC_HIP(hipMemcpyAsync(F.entries.p, all.data(), sizeof(uint4) * all.size(),
+    EPIC_HIP(hipMemcpyAsync(F.entries.p, packed.data(), sizeof(uint2) * packed.size(),
                             hipMemcpyHostToDevice, s));
     EPIC_HIP(hipMemcpyAsync(F.tw.p, tw.data(), sizeof(int2) * tw.size(), hipMemcpyHostToDevice, s));
     EPIC_HIP(hipStreamSynchronize(s));
@@ -369,27 +539,26 @@ epic_status fixed_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, i
                              hipStream_t s, bool dry) {
     const FixedPlan &F = p->fixed;
     const size_t lds = sizeof(uint2) * ((size_t)FN * FROW + (size_t)p->A);
-    epic_status st = p->P == 2 ? lds_ready(reinterpret_cast<const void *>(k_fixed64<2>), lds)
-                               : lds_ready(reinterpret_cast<const void *>(k_fixed64<1>), lds);
+    const bool halve = F.mask == 0xFFFu;
+    auto kern = p->P == 2 ? (halve ? k_fixed64<2, true> : k_fixed64<2, false>)
+                          : (halve ? k_fixed64<1, true> : k_fixed64<1, false>);
+    epic_status st = lds_ready(reinterpret_cast<const void *>(kern), lds);
     if (st || dry) return st;
+    // one element per thread: the kernel adds the self-term sums itself
+    int32_t *autos = p->A <= FT ? acc->d_autos.as<int32_t>() : nullptr;
     const int tps = (n_time + F.slices - 1) / F.slices;
     const int used = (n_time + tps - 1) / tps;            // slices with samples
     double *part = acc->d_work.as<double>();
     dim3 grid((unsigned)(F.n_items * used));
-    if (p->P == 2)
-        hipLaunchKernelGGL(k_fixed64<2>, grid, dim3(FT), lds, s, F.items.as<FusedItem>(),
-                           F.n_items, F.entries.as<uint4>(), d_volt, p->vstride(), p->A, n_time,
-                           tps, F.tw.as<int2>(), F.ts, F.mask, F.sg, part, p->vb);
-    else
-        hipLaunchKernelGGL(k_fixed64<1>, grid, dim3(FT), lds, s, F.items.as<FusedItem>(),
-                           F.n_items, F.entries.as<uint4>(), d_volt, p->vstride(), p->A, n_time,
-                           tps, F.tw.as<int2>(), F.ts, F.mask, F.sg, part, p->vb);
+    hipLaunchKernelGGL(kern, grid, dim3(FT), lds, s, F.items.as<FusedItem>(), F.n_items,
+                       F.entries.as<uint2>(), d_volt, p->vstride(), p->A, n_time, tps,
+                       F.tw.as<int2>(), F.ts, F.mask, F.sg, part, p->vb, autos);
     EPIC_HIP(hipGetLastError());
     dim3 rg(FN * FN / 256, p->n_prod, F.n_items);
     hipLaunchKernelGGL(k_fixed_reduce, rg, dim3(256), 0, s, F.items.as<FusedItem>(), F.n_items,
                        used, p->n_prod, part, std::ldexp(1.0, F.exp2), acc->d_acc.as<float>());
     EPIC_HIP(hipGetLastError());
-    return autos_accumulate(p, acc, d_volt, n_time, s);
+    return autos ? EPIC_OK : autos_accumulate(p, acc, d_volt, n_time, s);
 }
 
 }  // namespace epic
