@@ -69,6 +69,65 @@ template <> __device__ __forceinline__ void dft<8>(float2 *v) {
     }
 }
 
+// Length-8 DFT of v[q] w^q: every twiddle goes into the radix-2 butterfly that
+// follows it.  With w = c (1 + i t), a +- w b takes two fused multiply-adds for
+// u = (1 + i t) b and four for a +- c u, so the transform with its seven
+// twiddles costs 72 instructions instead of 52 + 28.  c = 0 is held as c =
+// 2^-40, t = 2^40, whose products are exact.
+struct Root {
+    float t, c;
+};
+struct Tw8 {
+    Root w4, w2, w1, w1e;                // w^4, w^2, w, w exp(2 pi i / 8)
+};
+__device__ __forceinline__ void bfly(float2 &a, float2 &b, Root r) {
+    const float u = fmaf(-r.t, b.y, b.x), v = fmaf(r.t, b.x, b.y);
+    b = make_float2(fmaf(-r.c, u, a.x), fmaf(-r.c, v, a.y));
+    a = make_float2(fmaf(r.c, u, a.x), fmaf(r.c, v, a.y));
+}
+__device__ __forceinline__ void bfly_i(float2 &a, float2 &b, Root r) {     // a +- i w b
+    const float u = fmaf(-r.t, b.y, b.x), v = fmaf(r.t, b.x, b.y);
+    b = make_float2(fmaf(r.c, v, a.x), fmaf(-r.c, u, a.y));
+    a = make_float2(fmaf(-r.c, v, a.x), fmaf(r.c, u, a.y));
+}
+// The last two stages: e[q] = v[q] + w^4 v[q+4], o[q] = v[q] - w^4 v[q+4].
+__device__ __forceinline__ void dft8_tail(float2 *v, float2 *e, float2 *o, Root w2, Root w1, Root w1e) {
+    bfly(e[0], e[2], w2);
+    bfly(e[1], e[3], w2);
+    bfly(e[0], e[1], w1);
+    bfly_i(e[2], e[3], w1);
+    bfly_i(o[0], o[2], w2);
+    bfly_i(o[1], o[3], w2);
+    bfly(o[0], o[1], w1e);
+    bfly_i(o[2], o[3], w1e);
+    v[0] = e[0];
+    v[4] = e[1];
+    v[2] = e[2];
+    v[6] = e[3];
+    v[1] = o[0];
+    v[5] = o[1];
+    v[3] = o[2];
+    v[7] = o[3];
+}
+__device__ __forceinline__ void dft8_tw(float2 *v, const Tw8 &w) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bfly(v[q], v[q + 4], w.w4);
+    float2 e[4] = {v[0], v[1], v[2], v[3]}, o[4] = {v[4], v[5], v[6], v[7]};
+    dft8_tail(v, e, o, w.w2, w.w1, w.w1e);
+}
+// The same with w = exp(2 pi i / 16): the first stage's twiddle is i.
+__device__ __forceinline__ void dft8_root16(float2 *v) {
+    float2 e[4], o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        e[q] = cadd(v[q], mul_i(v[q + 4]));
+        o[q] = csub(v[q], mul_i(v[q + 4]));
+    }
+    dft8_tail(v, e, o, Root{1.f, 0.70710678118654752440f},
+              Root{0.41421356237309504880f, 0.92387953251128675613f},
+              Root{2.41421356237309504880f, 0.38268343236508977173f});
+}
+
 // Grid storage in LDS: with two feeds each element is a float4 (X re, X im,
 // Y re, Y im), so one 16-byte access serves both feeds; one feed is float2.
 template <int P> struct Grid;
@@ -243,7 +302,7 @@ __device__ __forceinline__ void gather_cells(Grid<P> grid, const uint4 *ent, int
         }
 #pragma unroll
         for (int k = 0; k < GB; ++k) {
-            if (k0 + k >= n_iter) break;            // uniform: n_iter is per item
+            if (k0 + k >= n_iter) break;            // uniform: n_iter is per wave
             const float4 v = stage[e[k].x & 0xFFFFu];
             const float wr = __uint_as_float(e[k].z), wi = __uint_as_float(e[k].w);
             sx.x = fmaf(-wi, v.y, fmaf(wr, v.x, sx.x));
@@ -293,7 +352,7 @@ __device__ __forceinline__ void fused_item(const FusedItem &it,
                                            int frame_len, float *__restrict__ frames,
                                            int64_t fstride, int vb, int slice,
                                            float *__restrict__ part, int64_t part_stride, int tid,
-                                           float4 *gsm, float4 *stage, bool store) {
+                                           float4 *gsm, float4 *stage, bool store, int n_iter) {
     constexpr int T = FCfg<M>::T, RA = FCfg<M>::RA;
     constexpr int NPIX = M * M / T;
     constexpr int NPROD = P == 2 ? 4 : 1;
@@ -328,7 +387,6 @@ __device__ __forceinline__ void fused_item(const FusedItem &it,
 
     const uint8_t *vbase = volt + (int64_t)it.c * P * A * vb;
     const uint4 *ent = entries + it.entry_off + tid;
-    const int n_iter = it.n_iter;
     const bool own_autos = store && autos != nullptr && it.ox == 0 && it.oy == 0;
     int sa[AR][NPROD];
 #pragma unroll
@@ -469,12 +527,13 @@ __global__ __launch_bounds__(FCfg<M>::T) __attribute__((amdgpu_waves_per_eu(4)))
     extern __shared__ float4 smem[];
     float4 *stage = reinterpret_cast<float4 *>(reinterpret_cast<float2 *>(smem) + P * GSZ);
     const int slice = blockIdx.x / n_items;
-    const FusedItem it = items[blockIdx.x % n_items];
+    const FusedItem &it = items[blockIdx.x % n_items];
     if (it.c < 0) return;
     const int t_begin = slice * tps, t_stop = min(n_time, t_begin + tps);
+    const int n_iter = it.wave_iter[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
     fused_item<M, P, AR, FR, JN>(it, entries, volt, volt_t_stride, A, t_begin, t_stop, acc, autos,
                                  frame_len, frames, fstride, vb, slice, part, part_stride,
-                                 (int)threadIdx.x, smem, stage, true);
+                                 (int)threadIdx.x, smem, stage, true, n_iter);
 }
 
 // ------------------------------------------------- persistent work queue
@@ -526,26 +585,28 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
         if (M == 64) {
             if (sl >= qs.used[0]) continue;   // a slice beyond this call's samples
             const int t_begin = sl * qs.tps[0], t_stop = min(n_time, t_begin + qs.tps[0]);
-            const FusedItem it = qs.it[0][q->idx[0]];
+            const FusedItem &it = qs.it[0][q->idx[0]];
+            const int wi = it.wave_iter[__builtin_amdgcn_readfirstlane(tid >> 6)];
             fused_item<64, P, 1, false, false>(it, qs.e[0], volt, vstride, A, t_begin, t_stop,
                                                acc, nullptr, 0, nullptr, 0, vb, sl, qs.part[0],
-                                               qs.pstride[0], tid, smem, stage, true);
+                                               qs.pstride[0], tid, smem, stage, true, wi);
         } else if (M == 32) {
             if (sl >= qs.used[1]) continue;
             const int t_begin = sl * qs.tps[1], t_stop = min(n_time, t_begin + qs.tps[1]);
             // sub-group index and grid base are wave-uniform
             const int sub = __builtin_amdgcn_readfirstlane(tid >> 7);
-            const FusedItem it = qs.it[1][q->idx[min(sub, n - 1)]];
+            const FusedItem &it = qs.it[1][q->idx[min(sub, n - 1)]];
+            const int wi = it.wave_iter[__builtin_amdgcn_readfirstlane((tid & 127) >> 6)];
             float4 *g = reinterpret_cast<float4 *>(reinterpret_cast<float2 *>(smem) +
                                                    sub * P * 32 * FCfg<32>::ROW);
             fused_item<32, P, 1, false, false>(it, qs.e[1], volt, vstride, A, t_begin, t_stop,
                                                acc, nullptr, 0, nullptr, 0, vb, sl, qs.part[1],
-                                               qs.pstride[1], tid & 127, g, stage, sub < n);
+                                               qs.pstride[1], tid & 127, g, stage, sub < n, wi);
         } else {
             if (sl >= qs.used[2]) continue;
             const int t_begin = sl * qs.tps[2], t_stop = min(n_time, t_begin + qs.tps[2]);
             const int sub = __builtin_amdgcn_readfirstlane(tid >> 6);
-            const FusedItem it = qs.it[2][q->idx[min(sub, n - 1)]];
+            const FusedItem &it = qs.it[2][q->idx[min(sub, n - 1)]];
             float4 *g = reinterpret_cast<float4 *>(reinterpret_cast<float2 *>(smem) +
                                                    sub * P * 16 * FCfg<16>::ROW);
             // parts of different channels stage into their own slot after
@@ -556,7 +617,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
                                       : stage;
             fused_item<16, P, 1, false, false>(it, qs.e[2], volt, vstride, A, t_begin, t_stop,
                                                acc, nullptr, 0, nullptr, 0, vb, sl, qs.part[2],
-                                               qs.pstride[2], tid & 63, g, st, sub < n);
+                                               qs.pstride[2], tid & 63, g, st, sub < n,
+                                               it.n_iter);
         }
         __syncthreads();                  // the unit's last LDS reads before the next unit
     }
@@ -565,19 +627,211 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 __global__ void k_queue_reset(unsigned int *head) { *head = 0u; }
 
 // ------------------------------------------------- paired-class kernel
-// For N = 2 M grids (M = 64) whose element rows span fewer than M rows and two
-// feeds, classes (ox, 0) and (ox, 1) share everything up to the y-pass: their
-// folded grids differ only by the per-row factor exp(+2 pi i jy / N), which
-// commutes with the transform along x.  One workgroup per (channel, ox)
-// grids once and runs the x-pass once; the first y-pass reads each column
-// segment once and writes both classes (the oy = 1 copy multiplied on load by
-// the row factors, into a second grid); the last y-pass feeds both classes'
-// products.  The span index j of every pass is the wave index, so twiddles
-// and row factors are wave-uniform (scalar registers).
-__device__ __forceinline__ float uni(float v) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+// For N = 2 M grids (M = 64) whose element rows span at most M rows and two
+// feeds, classes (ox, 0) and (ox, 1) share everything up to the y-pass.  With
+// the rows counted from the first one an element touches (which multiplies
+// both feeds' output by the same phase), row m of class oy carries the factor
+// exp(+2 pi i oy m / N), which commutes with the transform along x.  One
+// workgroup per (channel, ox) grids once, transforms along x once, and along y
+// once per class.
+//
+// A wave owns eight whole rows in the x-pass and eight whole columns in the
+// y-pass, so both radix-8 steps of an axis exchange inside the wave (LDS
+// operations of one wave execute in order: no barrier).  Two grids in LDS
+// alternate between samples, and a sample takes two barriers:
+//   phase 1: y-pass and products of sample t (grid t & 1, own columns), and
+//            the gather of sample t + 1 into the other grid;
+//   phase 2: x-pass of sample t + 1 (own rows), staging of sample t + 2.
+// In phase 1 the waves 0-3 (one per SIMD) gather first and the waves 4-7
+// transform first, so that each SIMD has one wave waiting on LDS and one
+// issuing arithmetic.  Bound: vector issue, 1015 instructions per thread and
+// sample on 8 waves and 4 SIMDs (79 % of the cycles; LDS is busy for 55 %).
+// LWA-like station (128 channels, 256 elements), 1000 samples: 4.6 ms.  With
+// workgroup-wide passes (five barriers a sample, both classes' inputs through
+// LDS, 1126 instructions) it took 5.23 ms; 250 samples with Jones kernels 1.29
+// against 2.26 ms, where every tap's two further rows waited for L2 in turn.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+constexpr int kPairRow = 65, kPairGrid = 64 * kPairRow;
+
+// y-pass of both classes on the wave's columns and the products; lane = column
+// c + 8 j.  Rows j + 8 q hold the input; class oy's second step leaves row
+// frequency b + 8 q in accumulator oy 8 + q of lane b.  The columns are zeroed.
+__device__ __forceinline__ void pair_y(float4 *col, int j, const Tw8 (&tw)[2], float (&av)[16][4]) {
+    Grid<2> g;
+    g.g = col;
+    const int ia = j * kPairRow, ib = j * 8 * kPairRow;
+    float2 vx[8], vy[8], ax[8], ay[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        g.load(ia + q * 8 * kPairRow, vx[q], vy[q]);
+        ax[q] = vx[q];
+        ay[q] = vy[q];
+    }
+    // each exchange's LDS latency is covered by the other class's arithmetic
+    auto exchange = [&](float2 *x, float2 *y) {
+        wave_sync();
+#pragma unroll
+        for (int p = 0; p < 8; ++p) g.store(ia + p * 8 * kPairRow, x[p], y[p]);
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) g.load(ib + q * kPairRow, x[q], y[q]);
+    };
+    auto products = [&](const float2 *x, const float2 *y, int s0) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            float *a = av[s0 + q];
+            a[0] = fmaf(x[q].x, x[q].x, fmaf(x[q].y, x[q].y, a[0]));
+            a[1] = fmaf(y[q].x, y[q].x, fmaf(y[q].y, y[q].y, a[1]));
+            a[2] = fmaf(x[q].x, y[q].x, fmaf(x[q].y, y[q].y, a[2]));
+            a[3] = fmaf(x[q].y, y[q].x, fmaf(-x[q].x, y[q].y, a[3]));
+        }
+    };
+    dft<8>(ax);
+    dft<8>(ay);
+    exchange(ax, ay);
+    dft8_root16(vx);
+    dft8_root16(vy);
+    exchange(vx, vy);
+    dft8_tw(ax, tw[0]);
+    dft8_tw(ay, tw[0]);
+    products(ax, ay, 0);
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g.zero(ib + q * kPairRow);
+    dft8_tw(vx, tw[1]);
+    dft8_tw(vy, tw[1]);
+    products(vx, vy, 8);
+}
+
+// x-pass on the wave's rows; lane = row r + 8 j.  The second step stores
+// frequency b + 8 q at column b + 8 q: natural order.
+__device__ __forceinline__ void pair_x(float4 *row, int j, const Tw8 &tw) {
+    Grid<2> g;
+    g.g = row;
+    float2 vx[8], vy[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g.load(j + 8 * q, vx[q], vy[q]);
+    dft<8>(vx);
+    dft<8>(vy);
+    wave_sync();
+#pragma unroll
+    for (int p = 0; p < 8; ++p) g.store(j + 8 * p, vx[p], vy[p]);
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g.load(8 * j + q, vx[q], vy[q]);
+    wave_sync();
+    dft8_tw(vx, tw);
+    dft8_tw(vy, tw);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g.store(j + 8 * q, vx[q], vy[q]);
+}
+
+// A gather entry in registers: element | cell << 16 | last-tap-of-cell << 31.
+struct PairTap {
+    uint32_t ac;
+    float wr, wi;
+};
+__device__ __forceinline__ PairTap pair_tap(uint4 e) {
+    return PairTap{e.x | (e.y << 16), __uint_as_float(e.z), __uint_as_float(e.w)};
+}
+// With Jones kernels a tap's three rows.
+struct JonesTap {
+    uint4 r[3];
+};
+
+// One sample's gather (see gather_cells); the lists do not change from sample
+// to sample, so the first 2 B taps of a lane stay in registers, and a batch's
+// staged voltages are read before its first sum.  Longer lists stream from L2.
+template <int B>
+__device__ __forceinline__ void pair_gather(float4 *grid, const uint4 *ent, int n_iter,
+                                            const float4 *stage, const PairTap (&held)[2 * B]) {
+    constexpr int T = 512;
+    float2 sx = make_float2(0.f, 0.f), sy = make_float2(0.f, 0.f);
+    auto batch = [&](const PairTap (&e)[B], int k0) {
+        float4 v[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) v[k] = stage[e[k].ac & 0xFFFFu];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            if (k0 + k >= n_iter) break;            // uniform: n_iter is per wave
+            const float wr = e[k].wr, wi = e[k].wi;
+            sx.x = fmaf(-wi, v[k].y, fmaf(wr, v[k].x, sx.x));
+            sx.y = fmaf(wi, v[k].x, fmaf(wr, v[k].y, sx.y));
+            sy.x = fmaf(-wi, v[k].w, fmaf(wr, v[k].z, sy.x));
+            sy.y = fmaf(wi, v[k].z, fmaf(wr, v[k].w, sy.y));
+            grid[(e[k].ac >> 16) & 0x7FFFu] = make_float4(sx.x, sx.y, sy.x, sy.y);
+            const bool last = (e[k].ac >> 31) != 0u;
+            sx = last ? make_float2(0.f, 0.f) : sx;
+            sy = last ? make_float2(0.f, 0.f) : sy;
+        }
+    };
+    PairTap e[B];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h * B >= n_iter) break;
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            e[k] = held[h * B + k];
+            asm volatile("" : "+v"(e[k].ac));       // decoded per sample, not kept decoded
+        }
+        batch(e, h * B);
+    }
+    // no load of an entry stays in flight past its batch: the y-pass after the
+    // gather would have to wait for it, and so for the newer voltage loads
+    for (int k0 = 2 * B; k0 < n_iter; k0 += B) {
+        const uint4 *p = ent + opaque_zero();
+#pragma unroll
+        for (int k = 0; k < B; ++k) e[k] = pair_tap(p[(int64_t)min(k0 + k, n_iter - 1) * T]);
+        batch(e, k0);
+    }
+}
+
+// The Jones gather: B taps of three rows at a time, the next batch (after the
+// last one, the next sample's first) loaded while one is applied; nxt holds
+// batch 0 on entry and on return.
+template <int B>
+__device__ __forceinline__ void pair_gather_jones(float4 *grid, const uint4 *ent, int n_iter,
+                                                  const float4 *stage, JonesTap (&nxt)[B]) {
+    constexpr int T = 512;
+    float2 sx = make_float2(0.f, 0.f), sy = make_float2(0.f, 0.f);
+    for (int k0 = 0; k0 < n_iter; k0 += B) {
+        JonesTap e[B];
+        float4 v[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            e[k] = nxt[k];
+            v[k] = stage[e[k].r[0].x & 0xFFFFu];
+        }
+        const uint4 *p = ent + opaque_zero();
+        const int k1 = k0 + B < n_iter ? k0 + B : 0;
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                nxt[k].r[r] = p[(int64_t)(min(k1 + k, n_iter - 1) * 3 + r) * T];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            if (k0 + k >= n_iter) break;            // uniform
+            const float wr = __uint_as_float(e[k].r[0].z), wi = __uint_as_float(e[k].r[0].w);
+            sx.x = fmaf(-wi, v[k].y, fmaf(wr, v[k].x, sx.x));
+            sx.y = fmaf(wi, v[k].x, fmaf(wr, v[k].y, sx.y));
+            jones_taps(&e[k].r[1], &e[k].r[2], v[k], sx, sy);
+            grid[e[k].r[0].y] = make_float4(sx.x, sx.y, sy.x, sy.y);
+            const bool last = (e[k].r[0].x >> 31) != 0u;
+            sx = last ? make_float2(0.f, 0.f) : sx;
+            sy = last ? make_float2(0.f, 0.f) : sy;
+        }
+    }
+}
+
+// Time slices as in k_fused: workgroup b takes item b % n_items and samples
+// [s tps, (s + 1) tps) of slice s = b / n_items, and with `part` given stores
+// its sums there for k_fused_reduce.  roots[n]: twiddles of w = exp(+2 pi i n / 128).
 template <int AR, bool FR, bool JN>
 __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict__ items,
                                                     const uint4 *__restrict__ entries,
@@ -586,36 +840,23 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
                                                     float *__restrict__ acc,
                                                     int32_t *__restrict__ autos, int frame_len,
                                                     float *__restrict__ frames, int64_t fstride,
-                                                    int vb) {
-    constexpr int M = 64, T = 512, ROW = 65, GSZ = M * ROW, S = 8;
+                                                    int vb, int n_items, int tps,
+                                                    float *__restrict__ part, int64_t part_stride,
+                                                    const Tw8 *__restrict__ roots) {
+    constexpr int T = 512;
     extern __shared__ float4 smem[];
-    Grid<2> g, h;
-    g.g = smem;
-    h.g = smem + GSZ;
-    float4 *stage = smem + 2 * GSZ;
+    float4 *stage = smem + 2 * kPairGrid;
 
-    const FusedItem it = items[blockIdx.x];
+    const int slice = blockIdx.x / n_items;
+    const FusedItem &it = items[blockIdx.x % n_items];
     if (it.c < 0) return;
+    const int t0 = slice * tps, t1 = min(n_time, t0 + tps);
     const int tid = threadIdx.x;
-    const int line = tid & 63;
-    const int j = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lo = tid & 7, j = (tid >> 3) & 7;
 
-    float2 tw[8], md[8];
-    {
-        const int N = it.N;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            double sn, cs;
-            sincospi(2.0 * (double)(p * j) / (double)M, &sn, &cs);
-            tw[p] = make_float2(uni((float)cs), uni((float)sn));
-            // folded row j + 8p holds grid row jy = ylo + ((m - ylo) mod M)
-            const int m = j + S * p;
-            const int jy = it.ylo + (((m - it.ylo) % M) + M) % M;
-            sincospi(2.0 * (double)(jy % N) / (double)N, &sn, &cs);
-            md[p] = make_float2(uni((float)cs), uni((float)sn));
-        }
-    }
-    for (int i = tid; i < GSZ; i += T) g.zero(i);
+    const Tw8 tw[2] = {roots[2 * j], roots[2 * j + 1]};   // x-pass and class 0; class 1
+    for (int i = tid; i < 2 * kPairGrid; i += T) smem[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
     float av[16][4];
 #pragma unroll
@@ -625,36 +866,23 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
 
     const uint8_t *vbase = volt + (int64_t)it.c * 2 * A * vb;
     const uint4 *ent = entries + it.entry_off + tid;
-    const int n_iter = it.n_iter;
+    const int n_iter = it.wave_iter[w];
     const bool own_autos = autos != nullptr && it.ox == 0;
     int sa[AR][4];
-#pragma unroll
-    for (int k = 0; k < AR; ++k)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sa[k][q] = 0;
-
-    // this sample's voltages for elements tid + k T, loaded one sample ahead
-    uint32_t rx[AR], ry[AR];
-#pragma unroll
-    for (int k = 0; k < AR; ++k) {
-        const int a = tid + k * T;
-        rx[k] = ry[k] = 0u;
-        if (a < A && n_time > 0) {
-            rx[k] = volt_raw(vbase, a, vb);
-            ry[k] = volt_raw(vbase, A + a, vb);
-        }
-    }
-    // lists longer than one batch (up to GB + NT entries; the LWA plan's
-    // reach 10) keep their tail in registers across the sample loop
-    constexpr int NT = (JN || AR > 2) ? 0 : 4;
-    uint4 tail[NT > 0 ? NT : 1];
-#pragma unroll
-    for (int k = 0; k < NT; ++k)
-        tail[k] = n_iter > GB ? ent[(int64_t)min(GB + k, n_iter - 1) * T] : make_uint4(0u, 0u, 0u, 0u);
-    for (int t = 0; t < n_time; ++t) {
+    uint32_t rx[AR], ry[AR];             // the next sample's voltages of elements tid + k T
+    auto fetch = [&](int t) {
         const uint8_t *vt = vbase + (int64_t)t * volt_t_stride;
-        uint4 e[GB];
-        gather_load<T, JN>(e, ent, 0, n_iter);
+#pragma unroll
+        for (int k = 0; k < AR; ++k) {
+            const int a = tid + k * T;
+            if (a < A && t < t1) {
+                rx[k] = volt_raw(vt, a, vb);
+                ry[k] = volt_raw(vt, A + a, vb);
+            }
+        }
+    };
+    auto put = [&](int t) {              // stage sample t, add its self terms
+        if (t >= t1) return;
 #pragma unroll
         for (int k = 0; k < AR; ++k) {
             const int a = tid + k * T;
@@ -670,88 +898,49 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
                 }
             }
         }
-        for (int a = tid + AR * T; a < A; a += T) {
-            const int2 vx = volt_at(vt, a, vb), vy = volt_at(vt, A + a, vb);
-            stage[a] = make_float4((float)vx.x, (float)vx.y, (float)vy.x, (float)vy.y);
-        }
-        __syncthreads();
+    };
+#pragma unroll
+    for (int k = 0; k < AR; ++k) {
+        rx[k] = ry[k] = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sa[k][q] = 0;
+    }
+    fetch(t0);
+    constexpr int HB = JN ? 1 : 5, JB = JN ? 3 : 1;
+    PairTap held[2 * HB];
+    JonesTap jt[JB];
+    if (JN) {
+#pragma unroll
+        for (int k = 0; k < JB; ++k)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) jt[k].r[r] = ent[(int64_t)(min(k, n_iter - 1) * 3 + r) * T];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 2 * HB; ++k) held[k] = pair_tap(ent[(int64_t)min(k, n_iter - 1) * T]);
+    }
+    put(t0);
+    fetch(t0 + 1);
+    __syncthreads();
 
-        if (t + 1 < n_time) {
-            const uint8_t *vn = vt + volt_t_stride;
-#pragma unroll
-            for (int k = 0; k < AR; ++k) {
-                const int a = tid + k * T;
-                if (a < A) {
-                    rx[k] = volt_raw(vn, a, vb);
-                    ry[k] = volt_raw(vn, A + a, vb);
-                }
-            }
-        }
-        gather_cells<T, 2, JN, NT>(g, ent, n_iter, stage, e, tail);
-        __syncthreads();
-
-        pass_a<M, 2, true>(g, tid, tw);
-        __syncthreads();
-        pass_b<M, 2, true>(g, tid);
-        __syncthreads();
-        // first y-pass for both classes: column `line`, rows j + 8 q
-        {
-            const int base = j * ROW + line;
-            float2 vx[8], vy[8], wx[8], wy[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                g.load(base + q * S * ROW, vx[q], vy[q]);
-                wx[q] = cmul(vx[q], md[q]);
-                wy[q] = cmul(vy[q], md[q]);
-            }
-            dft<8>(vx);
-            dft<8>(vy);
-            dft<8>(wx);
-            dft<8>(wy);
-#pragma unroll
-            for (int p = 1; p < 8; ++p) {
-                vx[p] = cmul(vx[p], tw[p]);
-                vy[p] = cmul(vy[p], tw[p]);
-                wx[p] = cmul(wx[p], tw[p]);
-                wy[p] = cmul(wy[p], tw[p]);
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                g.store(base + q * S * ROW, vx[q], vy[q]);
-                h.store(base + q * S * ROW, wx[q], wy[q]);
-            }
-        }
-        __syncthreads();
-        // last y-pass + Eq. 2 products for both classes; g is left zeroed
-        // (h is fully rewritten by the first y-pass of the next sample)
-#pragma unroll
-        for (int oy = 0; oy < 2; ++oy) {
-            const Grid<2> b = oy ? h : g;
-            const int base = j * 8 * ROW + line;
-            float2 vx[8], vy[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) b.load(base + q * ROW, vx[q], vy[q]);
-            dft<8>(vx);
-            dft<8>(vy);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (!oy) g.zero(base + q * ROW);
-                float *a = av[oy * 8 + q];
-                a[0] = fmaf(vx[q].x, vx[q].x, fmaf(vx[q].y, vx[q].y, a[0]));
-                a[1] = fmaf(vy[q].x, vy[q].x, fmaf(vy[q].y, vy[q].y, a[1]));
-                a[2] = fmaf(vx[q].x, vy[q].x, fmaf(vx[q].y, vy[q].y, a[2]));
-                a[3] = fmaf(vx[q].y, vy[q].x, fmaf(-vx[q].x, vy[q].y, a[3]));
-            }
-        }
-        if (FR && (t + 1) % frame_len == 0) {
+    for (int t = t0 - 1; t < t1; ++t) {
+        float4 *cur = smem + (t & 1) * kPairGrid, *oth = smem + ((t + 1) & 1) * kPairGrid;
+        // phase 1
+        auto gather = [&]() {
+            if constexpr (JN)
+                pair_gather_jones<JB>(oth, ent, n_iter, stage, jt);
+            else
+                pair_gather<HB>(oth, ent, n_iter, stage, held);
+        };
+        if (w < 4 && t + 1 < t1) gather();
+        if (t >= t0) pair_y(cur + 8 * w + lo, j, tw, av);
+        if (w >= 4 && t + 1 < t1) gather();
+        if (FR && t >= t0 && (t + 1) % frame_len == 0) {
             const int N = it.N;
             const int64_t plane = (int64_t)N * N;
             float *fr = frames + (int64_t)(t / frame_len) * fstride + it.img_off;
 #pragma unroll
             for (int s = 0; s < 16; ++s) {
-                const int oy = s >> 3, q = s & 7;
-                const int ky = 2 * unscramble<64>(j * 8 + q) + oy;
-                const int kx = 2 * unscramble<64>(line) + it.ox;
+                const int ky = 2 * (j + 8 * (s & 7)) + (s >> 3), kx = 2 * (8 * w + lo) + it.ox;
                 float *dst = fr + (int64_t)ky * N + kx;
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
@@ -760,19 +949,31 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
                 }
             }
         }
+        __syncthreads();
+        // phase 2
+        if (t + 1 < t1) {
+            put(t + 2);
+            fetch(t + 3);
+            pair_x(oth + (8 * w + lo) * kPairRow, j, tw[0]);
+            __syncthreads();
+        }
     }
 
-    const int N = it.N;
-    const int64_t plane = (int64_t)N * N;
     if (!FR) {
+        const int N = it.N;
+        const int64_t plane = (int64_t)N * N;
+        float *base = part ? part + slice * part_stride + it.part_off : acc + it.img_off;
 #pragma unroll
         for (int s = 0; s < 16; ++s) {
-            const int oy = s >> 3, q = s & 7;
-            const int ky = 2 * unscramble<64>(j * 8 + q) + oy;
-            const int kx = 2 * unscramble<64>(line) + it.ox;
-            float *dst = acc + it.img_off + (int64_t)ky * N + kx;
+            const int ky = 2 * (j + 8 * (s & 7)) + (s >> 3), kx = 2 * (8 * w + lo) + it.ox;
+            float *dst = base + (int64_t)ky * N + kx;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) dst[p * plane] += av[s][p];
+            for (int p = 0; p < 4; ++p) {
+                if (part)
+                    dst[p * plane] = av[s][p];
+                else
+                    dst[p * plane] += av[s][p];
+            }
         }
     }
     if (own_autos) {
@@ -848,7 +1049,16 @@ __global__ __launch_bounds__(256) void k_fused_reduce(const GroupChan *__restric
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < g.n_floats;
          i += (int64_t)gridDim.x * 256) {
         float s = 0.f;
-        for (int k = 0; k < S; ++k) s += part[k * part_stride + g.part_off + i];
+        const float *q = part + g.part_off + i;
+        int k = 0;
+        for (; k + 8 <= S; k += 8) {           // eight loads in flight
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = q[(k + u) * part_stride];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; k < S; ++k) s += q[k * part_stride];
         acc[g.img_off + i] += s;
     }
 }
@@ -864,35 +1074,68 @@ static int row_of(int M) {
 // Cells are dealt longest-first to the least-loaded of T lanes, so each cell
 // is summed by one lane in a fixed order and written once.  Appends
 // n_iter * T entries [iter][lane] (jones: n_iter * 3 * T, [iter][row][lane])
-// to all (padding entries are zero) and returns n_iter.
-int lpt_pack(std::vector<GatherTap> &taps, int T, std::vector<uint4> &all, bool jones) {
+// to all (padding entries are zero) and returns n_iter.  wave_iter: the lanes
+// are then sorted by the length of their lists, so that a few crowded cells
+// lengthen one wave's gather and not all of them (an LWA channel at 40 MHz has
+// cells of ten taps, but 4.5 taps a lane), and wave_iter[w] is the longest list
+// of wave w.  Eight waves run in pairs (w, w + 4) on the four SIMDs: the longest
+// and the shortest lists share one.
+int lpt_pack(const std::vector<GatherTap> &taps, int T, std::vector<uint4> &all, bool jones,
+             int32_t *wave_iter, bool banks) {
     const size_t n = taps.size();
-    std::stable_sort(taps.begin(), taps.end(),
-                     [](const GatherTap &x, const GatherTap &y) { return x.cell < y.cell; });
-    std::vector<std::pair<int, int>> runs;  // (start, count) per cell
-    for (size_t i = 0; i < n;) {
-        size_t k = i;
-        while (k < n && taps[k].cell == taps[i].cell) ++k;
-        runs.push_back({(int)i, (int)(k - i)});
-        i = k;
-    }
-    std::vector<int> order(runs.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int x, int y) { return runs[x].second > runs[y].second; });
+    // taps by cell, cells by descending tap count: counting sorts, stable (a
+    // band of hundreds of channels sorts millions of taps at plan time)
+    int n_cells = 0;
+    for (const GatherTap &t : taps) n_cells = std::max(n_cells, t.cell + 1);
+    std::vector<int> at(n_cells + 1, 0), sorted_tap(n);
+    for (const GatherTap &t : taps) ++at[t.cell + 1];
+    for (int c = 0; c < n_cells; ++c) at[c + 1] += at[c];
+    std::vector<std::pair<int, int>> runs;  // (start, count) per cell, into sorted_tap
+    int longest = 0;
+    for (int c = 0; c < n_cells; ++c)
+        if (at[c + 1] > at[c]) {
+            runs.push_back({at[c], at[c + 1] - at[c]});
+            longest = std::max(longest, at[c + 1] - at[c]);
+        }
+    for (size_t i = 0; i < n; ++i) sorted_tap[at[taps[i].cell]++] = (int)i;
+    std::vector<int> order(runs.size()), first(longest + 2, 0);
+    for (const auto &r : runs) ++first[longest - r.second + 1];
+    for (int k = 0; k <= longest; ++k) first[k + 1] += first[k];
+    for (size_t i = 0; i < runs.size(); ++i) order[first[longest - runs[i].second]++] = (int)i;
     std::vector<std::vector<int>> lane_runs(T);
     std::vector<int> load(T, 0);
     using LP = std::pair<int, int>;
-    std::priority_queue<LP, std::vector<LP>, std::greater<LP>> heap;
-    for (int l = 0; l < T; ++l) heap.push({0, l});
+    // one heap, or (banks) one per cell index mod 8: lane l then owns cells = l mod
+    // 8, so that eight neighbouring lanes' 16-byte stores meet distinct banks
+    const int nh = banks ? 8 : 1;
+    std::vector<std::priority_queue<LP, std::vector<LP>, std::greater<LP>>> heap(nh);
+    for (int l = 0; l < T; ++l) heap[l % nh].push({0, l});
     for (int r : order) {
-        LP top = heap.top();
-        heap.pop();
+        auto &h = heap[taps[sorted_tap[runs[r].first]].cell % nh];
+        LP top = h.top();
+        h.pop();
         lane_runs[top.second].push_back(r);
         load[top.second] += runs[r].second;
-        heap.push({load[top.second], top.second});
+        h.push({load[top.second], top.second});
     }
     const int n_iter = *std::max_element(load.begin(), load.end());
+    if (wave_iter) {
+        const int W = T / 64;
+        std::vector<std::vector<int>> sorted(T);
+        for (int k = 0; k < W; ++k) wave_iter[k] = 0;
+        for (int r = 0; r < nh; ++r) {           // within each residue, T / nh lanes
+            std::vector<int> lanes;
+            for (int l = r; l < T; l += nh) lanes.push_back(l);
+            std::stable_sort(lanes.begin(), lanes.end(),
+                             [&](int x, int y) { return load[x] > load[y]; });
+            for (size_t i = 0; i < lanes.size(); ++i) {
+                const int k = (int)i * nh / 64, w = W == 8 && k >= 4 ? 11 - k : k;
+                wave_iter[w] = std::max(wave_iter[w], load[lanes[i]]);
+                sorted[w * 64 + (int)i * nh % 64 + r].swap(lane_runs[lanes[i]]);
+            }
+        }
+        lane_runs.swap(sorted);
+    }
     const size_t off = all.size();
     const int rows = jones ? 3 : 1;
     all.resize(off + (size_t)n_iter * rows * T, make_uint4(0u, 0u, 0u, 0u));
@@ -901,7 +1144,7 @@ int lpt_pack(std::vector<GatherTap> &taps, int T, std::vector<uint4> &all, bool 
         int k = 0;
         for (int r : lane_runs[l])
             for (int i = 0; i < runs[r].second; ++i, ++k) {
-                const GatherTap &tp = taps[runs[r].first + i];
+                const GatherTap &tp = taps[sorted_tap[runs[r].first + i]];
                 const bool last = (i == runs[r].second - 1);
                 uint4 e;
                 e.x = (uint32_t)tp.ant | (last ? 0x80000000u : 0u);
@@ -923,7 +1166,8 @@ int lpt_pack(std::vector<GatherTap> &taps, int T, std::vector<uint4> &all, bool 
 // Gather entries of one item: the taps of class (ox, oy) folded modulo M
 // (with Jones kernels all four weights of a tap carry the same fold factor).
 static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::vector<double> &w,
-                            int c, int ox, int oy, int M, int T, std::vector<uint4> &all) {
+                            int c, int ox, int oy, int M, int T, std::vector<uint4> &all,
+                            int ylo = 0) {
     const int A = p->A, K = p->K, J = p->J;
     const int N = p->ch[c].N, R = p->ch[c].R, ROW = row_of(M);
     std::vector<GatherTap> taps;
@@ -947,7 +1191,7 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
                     fw[2 * m + 1] = (float)(wr0 * ci + wi0 * cr);
                 }
                 GatherTap tp;
-                tp.cell = (jy % M) * ROW + (jx % M);
+                tp.cell = ((jy - ylo) % M) * ROW + (jx % M);
                 tp.ant = a;
                 tp.wr = fw[0];
                 tp.wi = fw[1];
@@ -956,7 +1200,8 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
             }
     }
     const size_t off = all.size();
-    int n_iter = lpt_pack(taps, T, all, J == 4);
+    FusedItem fi{};
+    int n_iter = lpt_pack(taps, T, all, J == 4, fi.wave_iter, M == 64 && p->P == 2);
     const int rows = J == 4 ? 3 : 1;
     // the kernels load the first entries of every list unconditionally: an
     // item always has at least one (padding) row
@@ -964,6 +1209,7 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
         all.resize(off + (size_t)rows * T, make_uint4(0u, 0u, 0u, 0u));
         n_iter = 1;
     }
+    for (int32_t &k : fi.wave_iter) k = std::max(k, 1);
     // The kernels store the running sum at every entry, so padding (all-zero)
     // entries point at a slot no pass reads: column M of row (lane mod M).
     for (int k = 0; k < n_iter; ++k)
@@ -972,7 +1218,6 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
             if (e.x == 0u && e.y == 0u && e.z == 0u && e.w == 0u)
                 e.y = (uint32_t)((l % M) * ROW + M);
         }
-    FusedItem fi{};
     fi.c = c;
     fi.N = N;
     fi.R = R;
@@ -981,7 +1226,6 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
     fi.n_iter = n_iter;
     fi.entry_off = (int64_t)off;
     fi.img_off = p->ch[c].img_off;
-    fi.ylo = 0;
     return fi;
 }
 
@@ -1049,6 +1293,40 @@ static int64_t fused_slots(epic_plan p, int M) {
            : M == 32 ? fused_slots_t<32, 2, false>(p->A) : fused_slots_t<16, 2, false>(p->A);
 }
 
+// Time slices of a paired group's call.  One workgroup fills a CU, so the
+// call takes ceil(workgroups / CUs) rounds of (samples per slice + a start and
+// an end that cost about six samples); more than one slice adds the partial
+// image sets' write and read (at about 4 TB/s against 4.5 us per sample) and
+// the reduction's launch.  The cheapest count wins: 1 where the items alone
+// fill whole rounds (128 channels on 256 CUs), 64 for one channel.  Frames
+// need no partial sets, only slices of whole frames.
+static int pair_slices(int64_t n_items, int64_t n_cu, int n_time, int s_max, int64_t part_floats,
+                       int unit) {
+    int best = 1;
+    double best_cost = 0.0;
+    for (int S = 1; S <= s_max; ++S) {
+        const int64_t tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
+        const int64_t used = (n_time + tps - 1) / tps;
+        if (used != S) continue;
+        const double rounds = std::ceil((double)(n_items * used) / (double)n_cu);
+        const double sets = unit > 1 || S == 1 ? 0.0 : 1.0 + (double)S * part_floats * 8.0 / 18e6;
+        const double cost = rounds * ((double)tps + 6.0) + sets;
+        if (S == 1 || cost < 0.97 * best_cost) {
+            best = S;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+static int cu_count() {
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 256;
+    return n_cu;
+}
+
 // Time slices of a one-class-per-item group: at least enough workgroups for
 // about four waves per SIMD (1024 SIMDs), then the fewest slices (at most 16)
 // whose last round of resident workgroups is at least 90 % full; each
@@ -1073,6 +1351,7 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
         }
     }
     if (p->time_slices > 0) S = p->time_slices;   // the caller's (autotuned) choice
+    g->real_items = real;
     g->slices = g->kind == 0 ? S : 1;
     std::vector<int64_t> off(p->C, -1);
     std::vector<GroupChan> chans;
@@ -1089,6 +1368,13 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
     }
     g->part_floats = n;
     g->n_chans = (int)chans.size();
+    if (g->kind == 1 && p->time_slices == 0) {
+        // room for the most slices that a call would take (pair_slices), at
+        // most 64 and 256 MiB of partial image sets
+        const int cap = (int)std::min<int64_t>(64, (int64_t{256} << 20) / (4 * std::max<int64_t>(1, n)));
+        for (int nt = 4; nt <= 65536; nt *= 2)
+            g->slices = std::max(g->slices, pair_slices(real, cu_count(), nt, std::max(1, cap), n, 1));
+    }
     epic_status st;
     if ((st = g->chans.alloc(sizeof(GroupChan) * std::max<size_t>(1, chans.size())))) return st;
     if (!chans.empty())
@@ -1189,6 +1475,23 @@ static epic_status queue_build(epic_plan p, hipStream_t s) {
     return EPIC_OK;
 }
 
+// The butterfly constants of w = exp(+2 pi i n / 128), n < 16 (k_fused_pair).
+static Root root_of(double turns) {
+    const double c = std::cos(2.0 * M_PI * turns), s = std::sin(2.0 * M_PI * turns);
+    if (std::fabs(c) < 1e-9) return Root{s > 0 ? 0x1p40f : -0x1p40f, 0x1p-40f};
+    return Root{(float)(s / c), (float)c};
+}
+static epic_status pair_roots(FusedGroup *g, hipStream_t s) {
+    std::vector<Tw8> r(16);
+    for (int n = 0; n < 16; ++n)
+        r[n] = Tw8{root_of(4 * n / 128.0), root_of(2 * n / 128.0), root_of(n / 128.0),
+                   root_of(n / 128.0 + 0.125)};
+    if (epic_status st = g->roots.alloc(sizeof(Tw8) * r.size())) return st;
+    EPIC_HIP(hipMemcpyAsync(g->roots.p, r.data(), sizeof(Tw8) * r.size(), hipMemcpyHostToDevice, s));
+    EPIC_HIP(hipStreamSynchronize(s));
+    return EPIC_OK;
+}
+
 epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vector<double> &w,
                         hipStream_t s) {
     const int A = p->A, K = p->K;
@@ -1212,9 +1515,7 @@ epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vect
         for (int c = 0; c < p->C; ++c) {
             if (pair_ylo[c] < 0) continue;
             for (int ox = 0; ox < 2; ++ox) {
-                FusedItem fi = build_item(p, j0, w, c, ox, 0, 64, 512, all);
-                fi.ylo = pair_ylo[c];
-                items.push_back(fi);
+                items.push_back(build_item(p, j0, w, c, ox, 0, 64, 512, all, pair_ylo[c]));
             }
         }
         if (!items.empty()) {
@@ -1222,6 +1523,7 @@ epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vect
             g->M = 64;
             g->kind = 1;
             p->groups.push_back(g);
+            if (epic_status st = pair_roots(g, s)) return st;
             epic_status st = upload_group(p, g, items, all, p->C, s);
             if (st) return st;
         }
@@ -1326,37 +1628,49 @@ static epic_status launch_fused(const FusedGroup *g, const uint8_t *d_volt, int6
 template <int AR, bool FR, bool JN>
 static epic_status launch_pair_fr(const FusedGroup *g, const uint8_t *d_volt, int64_t vstride,
                                   int A, int vb, int n_time, float *acc, int32_t *autos,
-                                  const FrameOut &fo, hipStream_t s, bool dry) {
-    const size_t lds = sizeof(float4) * (2 * 64 * 65 + (size_t)A);
+                                  const FrameOut &fo, hipStream_t s, bool dry, float *part) {
+    const size_t lds = sizeof(float4) * (2 * (size_t)kPairGrid + (size_t)A);
     auto kern = k_fused_pair<AR, FR, JN>;
     epic_status st = lds_ready(reinterpret_cast<const void *>(kern), lds);
     if (st || dry) return st;
-    hipLaunchKernelGGL(kern, dim3(g->n_items), dim3(512), lds, s, g->items.as<FusedItem>(),
+    const int unit = FR ? fo.len : 1;
+    const int want = FR ? 64 : part && acc ? g->slices : 1;
+    const int S = pair_slices(g->real_items, cu_count(), n_time, want, g->part_floats, unit);
+    const int tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
+    float *sets = !FR && S > 1 ? part : nullptr;
+    hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(512), lds, s, g->items.as<FusedItem>(),
                        g->entries.as<uint4>(), d_volt, vstride, A, n_time, acc, autos, fo.len,
-                       fo.out, fo.stride, vb);
+                       fo.out, fo.stride, vb, g->n_items, tps, sets, g->part_floats,
+                       g->roots.as<Tw8>());
     EPIC_HIP(hipGetLastError());
+    if (sets) {
+        hipLaunchKernelGGL(k_fused_reduce, dim3(64, g->n_chans), dim3(256), 0, s,
+                           g->chans.as<GroupChan>(), S, sets, g->part_floats, acc);
+        EPIC_HIP(hipGetLastError());
+    }
     return EPIC_OK;
 }
 
 template <int AR, bool JN>
 static epic_status launch_pair_ar(const FusedGroup *g, const uint8_t *d_volt, int64_t vstride,
                                   int A, int vb, int n_time, float *acc, int32_t *autos,
-                                  const FrameOut &fo, hipStream_t s, bool dry) {
+                                  const FrameOut &fo, hipStream_t s, bool dry, float *part) {
     return fo.len ? launch_pair_fr<AR, true, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos,
-                                                 fo, s, dry)
+                                                 fo, s, dry, nullptr)
                   : launch_pair_fr<AR, false, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos,
-                                                  fo, s, dry);
+                                                  fo, s, dry, part);
 }
 
 template <bool JN>
 static epic_status launch_pair(const FusedGroup *g, const uint8_t *d_volt, int64_t vstride, int A,
                                int vb, int n_time, float *acc, int32_t *autos, const FrameOut &fo,
-                               hipStream_t s, bool dry) {
+                               hipStream_t s, bool dry, float *part) {
+    // the LDS left beside the two grids holds 1920 elements
     if (A <= 512)
-        return launch_pair_ar<1, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry);
+        return launch_pair_ar<1, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry, part);
     if (A <= 1024)
-        return launch_pair_ar<2, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry);
-    return launch_pair_ar<4, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry);
+        return launch_pair_ar<2, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry, part);
+    return launch_pair_ar<4, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry, part);
 }
 
 // One persistent launch over the plan's work queue (EPIC_BATCH_QUEUE).
@@ -1457,9 +1771,9 @@ epic_status fused_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, i
                           ? reinterpret_cast<float *>(acc->d_work.as<char>() + g->work_off)
                           : nullptr;
         if (g->kind == 1 && p->J == 4) {
-            st = launch_pair<true>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry);
+            st = launch_pair<true>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part);
         } else if (g->kind == 1) {
-            st = launch_pair<false>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry);
+            st = launch_pair<false>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part);
         } else if (p->J == 4) {
             if (g->M == 64) st = launch_fused<64, 2, true>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part);
             if (g->M == 32) st = launch_fused<32, 2, true>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part);

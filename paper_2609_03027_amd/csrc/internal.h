@@ -70,10 +70,9 @@ struct FusedItem {
     int32_t R;
     int32_t ox, oy;
     int32_t n_iter;      // gather iterations (entries per lane)
+    int32_t wave_iter[8]; // fused kernels: the same per wave (at most n_iter)
     int64_t entry_off;   // first entry (uint4) of this item
     int64_t img_off;     // float offset of channel c in the image set
-    int32_t ylo;         // paired items: first grid row of the M-row window
-    int32_t pad;
     int64_t part_off;    // float offset of channel c in its group's partial image set
 };
 
@@ -103,13 +102,16 @@ struct FusedGroup {
     int M = 0;
     int kind = 0;     // 0: one class per item; 1: paired classes (ox, 0) + (ox, 1)
     int n_items = 0;
+    int64_t real_items = 0;  // without the empty items of the XCD layout
     DevBuf items;     // FusedItem[n_items]
     DevBuf entries;   // uint4 gather entries
+    DevBuf roots;     // kind 1: twiddle constants
     std::vector<FusedItem> host_items;
     // Time slices: with too few waves to fill the chip, each item's samples
     // are split over `slices` workgroups, each storing its Eq. 2 sums to its
     // own partial image set (part_floats floats, in the accumulator's working
     // memory at byte offset work_off); k_fused_reduce adds them in order.
+    // Paired groups: the most slices a call may take (pair_slices chooses).
     int slices = 1;
     int64_t part_floats = 0;
     int64_t work_off = 0;
@@ -357,7 +359,10 @@ struct GatherTap {
 // {ant | last << 31, cell, wr, wi}; returns the iterations per lane.  With
 // jones each iteration has three rows [iter][3][lane]: that entry, then
 // {xy re, xy im, yx re, yx im} and {yy re, yy im, 0, 0}.
-int lpt_pack(std::vector<GatherTap> &taps, int T, std::vector<uint4> &all, bool jones = false);
+// wave_iter (T / 64 values, optional): lanes sorted by list length, the
+// longest list of every wave returned.  banks: lane l owns cells = l mod 8.
+int lpt_pack(const std::vector<GatherTap> &taps, int T, std::vector<uint4> &all, bool jones = false,
+             int32_t *wave_iter = nullptr, bool banks = false);
 // Allow a kernel the device's whole LDS once, then check a launch's need.
 epic_status lds_ready(const void *kern, size_t lds);
 
