@@ -128,6 +128,80 @@ __device__ __forceinline__ void dft8_root16(float2 *v) {
               Root{2.41421356237309504880f, 0.38268343236508977173f});
 }
 
+// Length 4 likewise, w^2 and w: 24 instructions instead of 16 + 12.
+struct Tw4 {
+    Root w2, w1;
+};
+__device__ __forceinline__ void dft4_tw(float2 *v, const Tw4 &w) {
+    bfly(v[0], v[2], w.w2);
+    bfly(v[1], v[3], w.w2);
+    bfly(v[0], v[1], w.w1);
+    bfly_i(v[2], v[3], w.w1);
+    const float2 t = v[1];              // (X0, X2, X1, X3) -> natural order
+    v[1] = v[2];
+    v[2] = t;
+}
+
+// The constants of w = exp(+2 pi i n / L), from compile-time series (|x| <= pi,
+// 2 n / L <= 1 / 2: exact to FP64 rounding before they are rounded to FP32).
+constexpr double kPi = 3.14159265358979323846;
+constexpr double series_cos(double x) {
+    double s = 1.0, t = 1.0;
+    for (int k = 1; k < 24; ++k) {
+        t *= -x * x / ((2.0 * k - 1.0) * (2.0 * k));
+        s += t;
+    }
+    return s;
+}
+constexpr double series_sin(double x) {
+    double s = x, t = x;
+    for (int k = 1; k < 24; ++k) {
+        t *= -x * x / ((2.0 * k) * (2.0 * k + 1.0));
+        s += t;
+    }
+    return s;
+}
+constexpr Root root_of(int n, int L) {
+    if (4 * n == L) return Root{0x1p40f, 0x1p-40f};
+    const double x = 2.0 * kPi * n / L, c = series_cos(x);
+    return Root{(float)(series_sin(x) / c), (float)c};
+}
+constexpr Tw8 tw8_of(int n, int L) {     // 8 divides L
+    return Tw8{root_of(4 * n, L), root_of(2 * n, L), root_of(n, L), root_of(n + L / 8, L)};
+}
+constexpr Tw4 tw4_of(int n, int L) { return Tw4{root_of(2 * n, L), root_of(n, L)}; }
+struct RootTables {
+    Tw8 r8[16];                          // exp(+2 pi i n / 128): 64-point lines take even n
+    Tw4 r4[8];                           // exp(+2 pi i n / 32): 16-point lines take even n
+    Tw4 r96[24], r48[12];                // exp(+2 pi i n / 96), exp(+2 pi i n / 48)
+};
+constexpr RootTables root_tables() {
+    RootTables t{};
+    for (int n = 0; n < 16; ++n) t.r8[n] = tw8_of(n, 128);
+    for (int n = 0; n < 8; ++n) t.r4[n] = tw4_of(n, 32);
+    for (int n = 0; n < 24; ++n) t.r96[n] = tw4_of(n, 96);
+    for (int n = 0; n < 12; ++n) t.r48[n] = tw4_of(n, 48);
+    return t;
+}
+__constant__ constexpr RootTables kRoots = root_tables();
+
+// Twiddles of an M-point line's second step on the block of frequency p.
+template <int M> struct LineTw;
+template <> struct LineTw<64> {
+    using T = Tw8;
+    static __device__ __forceinline__ T at(int p) { return kRoots.r8[2 * p]; }
+};
+template <> struct LineTw<32> {
+    using T = Tw4;
+    static __device__ __forceinline__ T at(int p) { return kRoots.r4[p]; }
+};
+template <> struct LineTw<16> {
+    using T = Tw4;
+    static __device__ __forceinline__ T at(int p) { return kRoots.r4[2 * p]; }
+};
+__device__ __forceinline__ void dft_tw(float2 *v, const Tw8 &w) { dft8_tw(v, w); }
+__device__ __forceinline__ void dft_tw(float2 *v, const Tw4 &w) { dft4_tw(v, w); }
+
 // Grid storage in LDS: with two feeds each element is a float4 (X re, X im,
 // Y re, Y im), so one 16-byte access serves both feeds; one feed is float2.
 template <int P> struct Grid;
@@ -150,13 +224,14 @@ template <> struct Grid<1> {
     __device__ __forceinline__ void zero(int i) const { g[i] = make_float2(0.f, 0.f); }
 };
 
-// ------------------------------------------------------------ DIF passes
-// In-place decimation-in-frequency over one axis of an M x M grid stored
-// with row pitch ROW.  Pass A (radix RA, stride M/RA) multiplies output p by
-// exp(+2 pi i p j / M); pass B (radix RB, stride 1) has unit twiddles.  After
-// both passes position n of the axis holds frequency n / RB + RA (n % RB).
+// ------------------------------------------------------- line transforms
+// In place over one axis of an M x M grid stored with row pitch ROW.  Pass A
+// (radix RA, stride M/RA) leaves frequency p of span position j at j + p M/RA;
+// pass B (radix RB, stride 1) multiplies element q of block p by exp(+2 pi i
+// p q / M) on the way into its butterflies.  After both passes position n of
+// the axis holds frequency n / RB + RA (n % RB).
 template <int M, int P, bool ALONG_X>
-__device__ __forceinline__ void pass_a(Grid<P> g, int tid, const float2 *tw) {
+__device__ __forceinline__ void pass_a(Grid<P> g, int tid) {
     constexpr int RA = FCfg<M>::RA, ROW = FCfg<M>::ROW, S = M / RA;
     const int line = tid % M, j = tid / M;
     const int base = ALONG_X ? line * ROW + j : j * ROW + line;
@@ -167,20 +242,18 @@ __device__ __forceinline__ void pass_a(Grid<P> g, int tid, const float2 *tw) {
     dft<RA>(v0);
     if (P == 2) dft<RA>(v1);
 #pragma unroll
-    for (int p = 1; p < RA; ++p) {
-        v0[p] = cmul(v0[p], tw[p]);
-        if (P == 2) v1[p] = cmul(v1[p], tw[p]);
-    }
-#pragma unroll
     for (int q = 0; q < RA; ++q) g.store(base + q * step, v0[q], v1[q]);
 }
 
+// Butterflies of pass B per thread, and their twiddles.
+template <int M> constexpr int kNB = M * M / (FCfg<M>::RB * FCfg<M>::T);
+template <int M> using PassTw = typename LineTw<M>::T[kNB<M>];
+
 template <int M, int P, bool ALONG_X>
-__device__ __forceinline__ void pass_b(Grid<P> g, int tid) {
+__device__ __forceinline__ void pass_b(Grid<P> g, int tid, const PassTw<M> &tw) {
     constexpr int T = FCfg<M>::T, RB = FCfg<M>::RB, ROW = FCfg<M>::ROW;
-    constexpr int NB = M * M / (RB * T);
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
+    for (int k = 0; k < kNB<M>; ++k) {
         const int u = tid + k * T;
         const int line = u % M, blk = u / M;
         const int base = ALONG_X ? line * ROW + blk * RB : blk * RB * ROW + line;
@@ -188,8 +261,8 @@ __device__ __forceinline__ void pass_b(Grid<P> g, int tid) {
         float2 v0[RB], v1[RB];
 #pragma unroll
         for (int q = 0; q < RB; ++q) g.load(base + q * step, v0[q], v1[q]);
-        dft<RB>(v0);
-        if (P == 2) dft<RB>(v1);
+        dft_tw(v0, tw[k]);
+        if (P == 2) dft_tw(v1, tw[k]);
 #pragma unroll
         for (int q = 0; q < RB; ++q) g.store(base + q * step, v0[q], v1[q]);
     }
@@ -204,19 +277,19 @@ template <int M> __device__ __forceinline__ int unscramble(int n) {
 // accumulators av[k RB + q] and the grid is left zeroed for the next gather.
 // Output q of butterfly k sits at row blk RB + q, column line.
 template <int M, int P, int NPROD>
-__device__ __forceinline__ void pass_b_products(Grid<P> g, int tid, float (*av)[NPROD]) {
+__device__ __forceinline__ void pass_b_products(Grid<P> g, int tid, const PassTw<M> &tw,
+                                                float (*av)[NPROD]) {
     constexpr int T = FCfg<M>::T, RB = FCfg<M>::RB, ROW = FCfg<M>::ROW;
-    constexpr int NB = M * M / (RB * T);
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
+    for (int k = 0; k < kNB<M>; ++k) {
         const int u = tid + k * T;
         const int line = u % M, blk = u / M;
         const int base = blk * RB * ROW + line;
         float2 v0[RB], v1[RB];
 #pragma unroll
         for (int q = 0; q < RB; ++q) g.load(base + q * ROW, v0[q], v1[q]);
-        dft<RB>(v0);
-        if (P == 2) dft<RB>(v1);
+        dft_tw(v0, tw[k]);
+        if (P == 2) dft_tw(v1, tw[k]);
 #pragma unroll
         for (int q = 0; q < RB; ++q) {
             g.zero(base + q * ROW);
@@ -353,30 +426,18 @@ __device__ __forceinline__ void fused_item(const FusedItem &it,
                                            int64_t fstride, int vb, int slice,
                                            float *__restrict__ part, int64_t part_stride, int tid,
                                            float4 *gsm, float4 *stage, bool store, int n_iter) {
-    constexpr int T = FCfg<M>::T, RA = FCfg<M>::RA;
+    constexpr int T = FCfg<M>::T;
     constexpr int NPIX = M * M / T;
     constexpr int NPROD = P == 2 ? 4 : 1;
     constexpr int GSZ = M * FCfg<M>::ROW;
     Grid<P> grid;
     grid.g = reinterpret_cast<decltype(grid.g)>(gsm);
 
-    float2 tw[RA];
-    {
-        // With M = 64 the span index j = tid / 64 is the wave index, so the
-        // twiddles are wave-uniform and can live in scalar registers.
-        const int j = M == 64 ? __builtin_amdgcn_readfirstlane(tid / M) : tid / M;
+    // with M = 64 the block index is the wave index: scalar loads and registers
+    PassTw<M> tw;
 #pragma unroll
-        for (int p = 0; p < RA; ++p) {
-            double sn, cs;
-            sincospi(2.0 * (double)(p * j) / (double)M, &sn, &cs);
-            float c = (float)cs, s = (float)sn;
-            if (M == 64) {
-                c = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(c)));
-                s = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s)));
-            }
-            tw[p] = make_float2(c, s);
-        }
-    }
+    for (int k = 0; k < kNB<M>; ++k)
+        tw[k] = LineTw<M>::at(M == 64 ? __builtin_amdgcn_readfirstlane(tid / M) : (tid + k * T) / M);
     for (int i = tid; i < GSZ; i += T) grid.zero(i);
 
     float av[NPIX][NPROD];
@@ -450,15 +511,15 @@ __device__ __forceinline__ void fused_item(const FusedItem &it,
         gather_cells<T, P, JN>(grid, ent, n_iter, stage, e);
         __syncthreads();
 
-        pass_a<M, P, true>(grid, tid, tw);
+        pass_a<M, P, true>(grid, tid);
         __syncthreads();
-        pass_b<M, P, true>(grid, tid);
+        pass_b<M, P, true>(grid, tid, tw);
         __syncthreads();
-        pass_a<M, P, false>(grid, tid, tw);
+        pass_a<M, P, false>(grid, tid);
         __syncthreads();
         // last pass + Eq. 2 products; the grid is left zeroed, and the stage
         // barrier of the next sample orders these writes before the gather
-        pass_b_products<M, P, NPROD>(grid, tid, av);
+        pass_b_products<M, P, NPROD>(grid, tid, tw, av);
         if (FR && (t + 1) % frame_len == 0) {
             const int N = it.N, R = it.R;
             const int64_t plane = (int64_t)N * N;
@@ -645,10 +706,11 @@ __global__ void k_queue_reset(unsigned int *head) { *head = 0u; }
 // In phase 1 the waves 0-3 (one per SIMD) gather first and the waves 4-7
 // transform first, so that each SIMD has one wave waiting on LDS and one
 // issuing arithmetic.  Bound: vector issue, 1015 instructions per thread and
-// sample on 8 waves and 4 SIMDs (79 % of the cycles; LDS is busy for 55 %).
-// LWA-like station (128 channels, 256 elements), 1000 samples: 4.6 ms.  With
+// sample on 8 waves and 4 SIMDs (77 % of the cycles; LDS is busy for 46 %).
+// LWA-like station (128 channels, 256 elements), 1000 samples: 4.43 ms (4.6 ms
+// with rows and columns in natural order, see pair_pos).  With
 // workgroup-wide passes (five barriers a sample, both classes' inputs through
-// LDS, 1126 instructions) it took 5.23 ms; 250 samples with Jones kernels 1.29
+// LDS, 1126 instructions) it took 5.23 ms; 250 samples with Jones kernels 1.27
 // against 2.26 ms, where every tap's two further rows waited for L2 in turn.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -658,9 +720,14 @@ __device__ __forceinline__ void wave_sync() {
 
 constexpr int kPairRow = 65, kPairGrid = 64 * kPairRow;
 
+// The gather puts grid row or column m = j + 8 q at position 8 j + q: a 16-byte
+// read serves 16 lanes at once, eight rows (or columns) of two neighbouring j,
+// whose positions then differ by eight: no bank is met twice.
+__host__ __device__ constexpr int pair_pos(int m) { return 8 * (m % 8) + m / 8; }
+
 // y-pass of both classes on the wave's columns and the products; lane = column
-// c + 8 j.  Rows j + 8 q hold the input; class oy's second step leaves row
-// frequency b + 8 q in accumulator oy 8 + q of lane b.  The columns are zeroed.
+// c + 8 j.  Class oy's second step leaves row frequency b + 8 q in accumulator
+// oy 8 + q of lane b.  The columns are zeroed.
 __device__ __forceinline__ void pair_y(float4 *col, int j, const Tw8 (&tw)[2], float (&av)[16][4]) {
     Grid<2> g;
     g.g = col;
@@ -668,7 +735,7 @@ __device__ __forceinline__ void pair_y(float4 *col, int j, const Tw8 (&tw)[2], f
     float2 vx[8], vy[8], ax[8], ay[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        g.load(ia + q * 8 * kPairRow, vx[q], vy[q]);
+        g.load(ib + q * kPairRow, vx[q], vy[q]);
         ax[q] = vx[q];
         ay[q] = vy[q];
     }
@@ -715,7 +782,7 @@ __device__ __forceinline__ void pair_x(float4 *row, int j, const Tw8 &tw) {
     g.g = row;
     float2 vx[8], vy[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) g.load(j + 8 * q, vx[q], vy[q]);
+    for (int q = 0; q < 8; ++q) g.load(8 * j + q, vx[q], vy[q]);
     dft<8>(vx);
     dft<8>(vy);
     wave_sync();
@@ -831,7 +898,7 @@ __device__ __forceinline__ void pair_gather_jones(float4 *grid, const uint4 *ent
 
 // Time slices as in k_fused: workgroup b takes item b % n_items and samples
 // [s tps, (s + 1) tps) of slice s = b / n_items, and with `part` given stores
-// its sums there for k_fused_reduce.  roots[n]: twiddles of w = exp(+2 pi i n / 128).
+// its sums there for k_fused_reduce.
 template <int AR, bool FR, bool JN>
 __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict__ items,
                                                     const uint4 *__restrict__ entries,
@@ -841,8 +908,7 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
                                                     int32_t *__restrict__ autos, int frame_len,
                                                     float *__restrict__ frames, int64_t fstride,
                                                     int vb, int n_items, int tps,
-                                                    float *__restrict__ part, int64_t part_stride,
-                                                    const Tw8 *__restrict__ roots) {
+                                                    float *__restrict__ part, int64_t part_stride) {
     constexpr int T = 512;
     extern __shared__ float4 smem[];
     float4 *stage = smem + 2 * kPairGrid;
@@ -855,7 +921,7 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = tid & 7, j = (tid >> 3) & 7;
 
-    const Tw8 tw[2] = {roots[2 * j], roots[2 * j + 1]};   // x-pass and class 0; class 1
+    const Tw8 tw[2] = {kRoots.r8[2 * j], kRoots.r8[2 * j + 1]};   // x-pass and class 0; class 1
     for (int i = tid; i < 2 * kPairGrid; i += T) smem[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
     float av[16][4];
@@ -989,6 +1055,374 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
     }
 }
 
+// ------------------------------------------------- row-unfolded kernel
+// Grids of side N = 3 M (96, 48) whose element rows span at most N / 2, two feeds.
+// One class per item grids the channel nine times and transforms all M rows of
+// every folded class.  Here an item is one class ox of the x axis (3 M columns
+// folded modulo M) with its rows unfolded: it grids once into N / 2 rows,
+// transforms them along x, and each of the three classes oy of the y axis folds the
+// rows it needs in registers: row m = j + S q (S = M / RA) carries
+// exp(+2 pi i oy m / N) = exp(2 pi i oy j / N) exp(2 pi i oy q / (3 RA)) and row m + M a
+// further exp(2 pi i oy / 3), so class oy is the transform of
+//   u_q = v_q + exp(2 pi i oy / 3) v_{q+RA}     (q < RA / 2, else u_q = v_q)
+// with the constant input twiddles exp(2 pi i oy / (3 RA)), and the factor of j
+// goes into the second step's twiddles, w = exp(2 pi i (3 p + oy) / N) on block p.
+// Rows are counted from the first one an element touches (see k_fused_pair).
+//
+// Waves own rows in the x-pass (16 at a time, dealt to the waves from one that
+// turns with the workgroup, since three groups on two waves leave half of the
+// SIMDs with twice the work) and columns in the y-pass: three barriers a sample.
+// Bound: vector issue and LDS latency at two waves per SIMD (the sums, the held
+// rows and two classes in work take 250 registers).  256 elements, 512 samples:
+// 81 channels of 96^2 1.22 ms against 1.98 with one class per item, 40 of 48^2 0.26
+// against 0.66.  192^2 in this form (12 rows a lane, MX = 32) took 7.5 ms for 139
+// channels against 7.3: two waves per SIMD instead of four cost it more than a
+// third of the arithmetic.
+template <int M_> struct RowsCfg {
+    static constexpr int M = M_;
+    static constexpr int RAX = M == 32 ? 8 : 4;        // x lines: RAX x 4
+    static constexpr int RA = M == 16 ? 4 : 8;         // y lines: RA x S
+    static constexpr int S = M / RA;
+    static constexpr int T = M * S;                    // threads
+    static constexpr int CW = 64 / S;                  // columns per wave
+    static constexpr int NB = RA / S;                  // second-step blocks per lane
+    static constexpr int QV = RA + RA / 2;             // rows per lane
+    static constexpr int ROW = M + 1;
+    static constexpr int H = QV * S;                   // rows in LDS: N / 2
+    static constexpr int N = 3 * M;
+    using Tw = Tw4;
+    // LDS row of grid row j + S q (cf. pair_pos): rows of one j lie together
+    static __host__ __device__ constexpr int row(int j, int q) {
+        return q < RA ? RA * j + q : M + (RA / 2) * j + q - RA;
+    }
+    static constexpr size_t lds(int A) {
+        return sizeof(float4) * ((size_t)H * ROW + A) + sizeof(Tw) * 3 * RA;
+    }
+};
+
+// Class oy of the first y step: fold, then transform with constant twiddles.
+template <int OY> __device__ __forceinline__ void rows_first(const float2 (&v)[12], float2 *u) {
+    constexpr Root third = root_of(OY, 3);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        u[q] = v[q];
+        if (q < 4) {
+            const float2 b = v[q + 8];
+            if (OY == 0)
+                u[q] = cadd(v[q], b);
+            else
+                u[q] = make_float2(fmaf(third.c, fmaf(-third.t, b.y, b.x), v[q].x),
+                                   fmaf(third.c, fmaf(third.t, b.x, b.y), v[q].y));
+        }
+    }
+    if (OY == 0) {
+        dft<8>(u);
+    } else {
+        constexpr Tw8 w = tw8_of(OY, 24);
+        dft8_tw(u, w);
+    }
+}
+template <int OY> __device__ __forceinline__ void rows_first(const float2 (&v)[6], float2 *u) {
+    constexpr Root third = root_of(OY, 3);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        u[q] = v[q];
+        if (q < 2) {
+            const float2 b = v[q + 4];
+            if (OY == 0)
+                u[q] = cadd(v[q], b);
+            else
+                u[q] = make_float2(fmaf(third.c, fmaf(-third.t, b.y, b.x), v[q].x),
+                                   fmaf(third.c, fmaf(third.t, b.x, b.y), v[q].y));
+        }
+    }
+    if (OY == 0) {
+        dft<4>(u);
+    } else {
+        constexpr Tw4 w = tw4_of(OY, 12);
+        dft4_tw(u, w);
+    }
+}
+
+// The gather (see gather_cells), with a batch's staged voltages read before its
+// first sum: the registers of the y-pass are free here, so twelve entries and
+// their voltages are in flight.  The first twelve are loaded by the caller.
+constexpr int RG = 12;
+template <int T>
+__device__ __forceinline__ void rows_load(uint4 (&e)[RG], const uint4 *ent, int k0, int n_iter) {
+    const uint4 *p = ent + opaque_zero();
+#pragma unroll
+    for (int k = 0; k < RG; ++k) e[k] = p[(int64_t)min(k0 + k, n_iter - 1) * T];
+}
+template <int T>
+__device__ __forceinline__ void rows_gather(float4 *grid, const uint4 *ent, int n_iter,
+                                            const float4 *stage, uint4 (&e)[RG]) {
+    constexpr int B = 4;
+    float2 sx = make_float2(0.f, 0.f), sy = make_float2(0.f, 0.f);
+    for (int k0 = 0; k0 < n_iter; k0 += RG) {
+        if (k0) rows_load<T>(e, ent, k0, n_iter);
+#pragma unroll
+        for (int h = 0; h < RG; h += B) {
+            if (k0 + h >= n_iter) break;             // uniform: n_iter is per wave
+            float4 v[B];
+#pragma unroll
+            for (int k = 0; k < B; ++k) v[k] = stage[e[h + k].x & 0xFFFFu];
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                if (k0 + h + k >= n_iter) break;
+                const float wr = __uint_as_float(e[h + k].z), wi = __uint_as_float(e[h + k].w);
+                sx.x = fmaf(-wi, v[k].y, fmaf(wr, v[k].x, sx.x));
+                sx.y = fmaf(wi, v[k].x, fmaf(wr, v[k].y, sx.y));
+                sy.x = fmaf(-wi, v[k].w, fmaf(wr, v[k].z, sy.x));
+                sy.y = fmaf(wi, v[k].z, fmaf(wr, v[k].w, sy.y));
+                grid[e[h + k].y] = make_float4(sx.x, sx.y, sy.x, sy.y);
+                const bool last = (e[h + k].x >> 31) != 0u;
+                sx = last ? make_float2(0.f, 0.f) : sx;
+                sy = last ? make_float2(0.f, 0.f) : sy;
+            }
+        }
+    }
+}
+
+// x-pass of 16 rows; lane = row r + 16 j.
+template <int M>
+__device__ __forceinline__ void rows_x(float4 *grid, int row, int j, const Tw4 *tw) {
+    using C = RowsCfg<M>;
+    constexpr int RAX = C::RAX, NBX = RAX / 4;
+    if (row >= C::H) return;
+    Grid<2> g;
+    g.g = grid + row * C::ROW;
+    {
+        float2 x[RAX], y[RAX];
+#pragma unroll
+        for (int q = 0; q < RAX; ++q) g.load(j + 4 * q, x[q], y[q]);
+        dft<RAX>(x);
+        dft<RAX>(y);
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < RAX; ++q) g.store(j + 4 * q, x[q], y[q]);
+    }
+    wave_sync();
+    float2 x[NBX][4], y[NBX][4];
+#pragma unroll
+    for (int k = 0; k < NBX; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g.load(4 * (j + 4 * k) + q, x[k][q], y[k][q]);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < NBX; ++k) {
+        dft4_tw(x[k], tw[k]);
+        dft4_tw(y[k], tw[k]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g.store(j + 4 * k + RAX * q, x[k][q], y[k][q]);
+    }
+}
+
+// y-pass of the wave's columns and the products of all three classes; the
+// column is left zeroed.  Sum slot (oy, k, q) holds frequency j + S k + RA q of
+// class oy.
+template <int M>
+__device__ __forceinline__ void rows_y(float4 *col, int j, const typename RowsCfg<M>::Tw *tw,
+                                       float (&av)[3][RowsCfg<M>::NB * RowsCfg<M>::S][4]) {
+    using C = RowsCfg<M>;
+    constexpr int RA = C::RA, S = C::S, NB = C::NB, QV = C::QV, ROW = C::ROW;
+    Grid<2> g;
+    g.g = col;
+    float2 vx[QV], vy[QV];
+#pragma unroll
+    for (int q = 0; q < QV; ++q) g.load(C::row(j, q) * ROW, vx[q], vy[q]);
+    wave_sync();
+#pragma unroll
+    for (int q = RA; q < QV; ++q) g.zero(C::row(j, q) * ROW);
+    // first-step outputs p at rows j + S p, read back as blocks j + S k
+    auto exchange = [&](float2 *x, float2 *y) {
+        wave_sync();
+#pragma unroll
+        for (int p = 0; p < RA; ++p) g.store((j + S * p) * ROW, x[p], y[p]);
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+#pragma unroll
+            for (int q = 0; q < S; ++q) g.load(((j + S * k) * S + q) * ROW, x[k * S + q], y[k * S + q]);
+    };
+    auto second = [&](float2 *x, float2 *y, int oy) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const typename C::Tw w = tw[oy * RA + j + S * k];
+            dft_tw(x + k * S, w);
+            dft_tw(y + k * S, w);
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const float2 ex = x[k * S + q], ey = y[k * S + q];
+                float *a = av[oy][k * S + q];
+                a[0] = fmaf(ex.x, ex.x, fmaf(ex.y, ex.y, a[0]));
+                a[1] = fmaf(ey.x, ey.x, fmaf(ey.y, ey.y, a[1]));
+                a[2] = fmaf(ex.x, ey.x, fmaf(ex.y, ey.y, a[2]));
+                a[3] = fmaf(ex.y, ey.x, fmaf(-ex.x, ey.y, a[3]));
+            }
+        }
+    };
+    // each exchange's LDS latency is covered by another class's arithmetic
+    float2 ax[RA], ay[RA], bx[RA], by[RA];
+    rows_first<0>(vx, ax);
+    rows_first<0>(vy, ay);
+    exchange(ax, ay);
+    rows_first<1>(vx, bx);
+    rows_first<1>(vy, by);
+    exchange(bx, by);
+    second(ax, ay, 0);
+    rows_first<2>(vx, ax);
+    rows_first<2>(vy, ay);
+    exchange(ax, ay);
+    second(bx, by, 1);
+    wave_sync();
+#pragma unroll
+    for (int p = 0; p < RA; ++p) g.zero((j + S * p) * ROW);
+    second(ax, ay, 2);
+}
+
+template <int M, int AR, bool FR>
+__global__ __launch_bounds__((RowsCfg<M>::T))
+__attribute__((amdgpu_waves_per_eu(M == 16 ? 3 : 2))) void k_fused_rows(
+    const FusedItem *__restrict__ items, const uint4 *__restrict__ entries,
+    const uint8_t *__restrict__ volt, int64_t volt_t_stride, int A, int n_time,
+    float *__restrict__ acc, int32_t *__restrict__ autos, int frame_len,
+    float *__restrict__ frames, int64_t fstride, int vb, int n_items, int tps,
+    float *__restrict__ part, int64_t part_stride) {
+    using C = RowsCfg<M>;
+    constexpr int T = C::T, W = T / 64, NP = C::NB * C::S, N = C::N;
+    extern __shared__ float4 smem[];
+    float4 *stage = smem + C::H * C::ROW;
+    typename C::Tw *twy = reinterpret_cast<typename C::Tw *>(stage + A);
+
+    const int slice = blockIdx.x / n_items;
+    const FusedItem &it = items[blockIdx.x % n_items];
+    if (it.c < 0) return;
+    const int t0 = slice * tps, t1 = min(n_time, t0 + tps);
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    Grid<2> grid;
+    grid.g = smem;
+    for (int i = tid; i < C::H * C::ROW; i += T) grid.zero(i);
+    if (tid < 3 * C::RA) {
+        const int n = 3 * (tid % C::RA) + tid / C::RA;      // 3 p + oy
+        if constexpr (M == 32) twy[tid] = kRoots.r96[n];
+        if constexpr (M == 16) twy[tid] = kRoots.r48[n];
+    }
+    Tw4 twx[C::RAX / 4];
+#pragma unroll
+    for (int k = 0; k < C::RAX / 4; ++k) twx[k] = LineTw<M>::at((lane >> 4) + 4 * k);
+
+    float av[3][NP][4];
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) av[o][k][q] = 0.f;
+
+    const uint8_t *vbase = volt + (int64_t)it.c * 2 * A * vb;
+    const uint4 *ent = entries + it.entry_off + tid;
+    const int n_iter = it.wave_iter[w];
+    // self terms here only with one element a thread (registers)
+    const bool own_autos = AR == 1 && autos != nullptr && it.ox == 0;
+    int sa[4] = {0, 0, 0, 0};
+    uint32_t rx[AR], ry[AR];             // the next sample's voltages of elements tid + k T
+    auto fetch = [&](int t) {
+        const uint8_t *vt = vbase + (int64_t)t * volt_t_stride;
+#pragma unroll
+        for (int k = 0; k < AR; ++k) {
+            const int a = tid + k * T;
+            if (a < A && t < t1) {
+                rx[k] = volt_raw(vt, a, vb);
+                ry[k] = volt_raw(vt, A + a, vb);
+            }
+        }
+    };
+    auto put = [&](int t) {              // stage sample t, add its self terms
+        if (t >= t1) return;
+#pragma unroll
+        for (int k = 0; k < AR; ++k) {
+            const int a = tid + k * T;
+            if (a < A) {
+                const int2 vx = volt_dec(rx[k], vb), vy = volt_dec(ry[k], vb);
+                const int xr = vx.x, xi = vx.y, yr = vy.x, yi = vy.y;
+                stage[a] = make_float4((float)xr, (float)xi, (float)yr, (float)yi);
+                if (own_autos) {
+                    sa[0] += xr * xr + xi * xi;
+                    sa[1] += yr * yr + yi * yi;
+                    sa[2] += xr * yr + xi * yi;
+                    sa[3] += xi * yr - xr * yi;
+                }
+            }
+        }
+        const uint8_t *vt = vbase + (int64_t)t * volt_t_stride;
+        for (int a = tid + AR * T; a < A; a += T) {
+            const int2 vx = volt_at(vt, a, vb), vy = volt_at(vt, A + a, vb);
+            stage[a] = make_float4((float)vx.x, (float)vx.y, (float)vy.x, (float)vy.y);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < AR; ++k) rx[k] = ry[k] = 0u;
+    fetch(t0);
+    put(t0);
+    fetch(t0 + 1);
+
+    const int col = w * C::CW + lane % C::CW, jy = lane / C::CW;
+    for (int t = t0; t < t1; ++t) {
+        uint4 e[RG];
+        rows_load<T>(e, ent, 0, n_iter);
+        __syncthreads();                 // staged voltages, zeroed grid
+        rows_gather<T>(smem, ent, n_iter, stage, e);
+        __syncthreads();
+        put(t + 1);
+        fetch(t + 2);
+        for (int g = (w + (int)blockIdx.x) % W; g < (C::H + 15) / 16; g += W)
+            rows_x<M>(smem, 16 * g + (lane & 15), lane >> 4, twx);
+        __syncthreads();
+        rows_y<M>(smem + col, jy, twy, av);
+        if (FR && (t + 1) % frame_len == 0) {
+            float *fr = frames + (int64_t)(t / frame_len) * fstride + it.img_off;
+#pragma unroll
+            for (int o = 0; o < 3; ++o)
+#pragma unroll
+                for (int k = 0; k < NP; ++k) {
+                    const int ky = 3 * (jy + C::S * (k / C::S) + C::RA * (k % C::S)) + o;
+                    float *dst = fr + (int64_t)ky * N + 3 * col + it.ox;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        dst[q * (int64_t)N * N] = av[o][k][q];
+                        av[o][k][q] = 0.f;
+                    }
+                }
+        }
+    }
+
+    if (!FR) {
+        float *base = part ? part + slice * part_stride + it.part_off : acc + it.img_off;
+#pragma unroll
+        for (int o = 0; o < 3; ++o)
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const int ky = 3 * (jy + C::S * (k / C::S) + C::RA * (k % C::S)) + o;
+                float *dst = base + (int64_t)ky * N + 3 * col + it.ox;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (part)
+                        dst[q * (int64_t)N * N] = av[o][k][q];
+                    else
+                        dst[q * (int64_t)N * N] += av[o][k][q];
+                }
+            }
+    }
+    if (own_autos && tid < A) {
+        int32_t *d = autos + ((int64_t)it.c * A + tid) * 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) atomicAdd(d + q, sa[q]);
+    }
+}
+
 // Per-element self-term sums S_a^{pq} = sum_t E_a^p conj(E_a^q), exact in
 // int32 (|E|^2 <= 128 per sample).  Grid: (elements, channels, time chunks).
 // VB bytes per voltage sample; eight samples' bytes are loaded at once.
@@ -1067,6 +1501,10 @@ __global__ __launch_bounds__(256) void k_fused_reduce(const GroupChan *__restric
 static int threads_of(int M) {
     return M == 64 ? FCfg<64>::T : M == 32 ? FCfg<32>::T : FCfg<16>::T;
 }
+static int threads_of(const FusedGroup *g) {
+    if (g->kind == 2) return g->M == 32 ? RowsCfg<32>::T : RowsCfg<16>::T;
+    return threads_of(g->M);
+}
 static int row_of(int M) {
     return M == 64 ? FCfg<64>::ROW : M == 32 ? FCfg<32>::ROW : FCfg<16>::ROW;
 }
@@ -1106,12 +1544,16 @@ int lpt_pack(const std::vector<GatherTap> &taps, int T, std::vector<uint4> &all,
     std::vector<int> load(T, 0);
     using LP = std::pair<int, int>;
     // one heap, or (banks) one per cell index mod 8: lane l then owns cells = l mod
-    // 8, so that eight neighbouring lanes' 16-byte stores meet distinct banks
+    // 8, so that eight neighbouring lanes' 16-byte stores meet distinct banks,
+    // unless another lane's list is shorter by more than a tap
     const int nh = banks ? 8 : 1;
     std::vector<std::priority_queue<LP, std::vector<LP>, std::greater<LP>>> heap(nh);
     for (int l = 0; l < T; ++l) heap[l % nh].push({0, l});
     for (int r : order) {
-        auto &h = heap[taps[sorted_tap[runs[r].first]].cell % nh];
+        int own = taps[sorted_tap[runs[r].first]].cell % nh;
+        for (int k = 0; k < nh; ++k)
+            if (heap[k].top().first + 1 < heap[own].top().first) own = k;
+        auto &h = heap[own];
         LP top = h.top();
         h.pop();
         lane_runs[top.second].push_back(r);
@@ -1167,11 +1609,18 @@ int lpt_pack(const std::vector<GatherTap> &taps, int T, std::vector<uint4> &all,
 // (with Jones kernels all four weights of a tap carry the same fold factor).
 static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::vector<double> &w,
                             int c, int ox, int oy, int M, int T, std::vector<uint4> &all,
-                            int ylo = 0) {
+                            int ylo = 0, bool unfold = false, bool pair = false) {
     const int A = p->A, K = p->K, J = p->J;
     const int N = p->ch[c].N, R = p->ch[c].R, ROW = row_of(M);
     std::vector<GatherTap> taps;
     taps.reserve((size_t)A * K * K);
+    // LDS cell of row y (from ylo) and folded column x
+    auto place = [&](int y, int x) {
+        if (pair) return pair_pos(y) * ROW + pair_pos(x);
+        if (!unfold) return (y % M) * ROW + x;
+        const int r = M == 32 ? RowsCfg<32>::row(y % 4, y / 4) : RowsCfg<16>::row(y % 4, y / 4);
+        return r * ROW + x;
+    };
     for (int a = 0; a < A; ++a) {
         const int jx0 = j0[((size_t)c * A + a) * 2];
         const int jy0 = j0[((size_t)c * A + a) * 2 + 1];
@@ -1191,7 +1640,7 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
                     fw[2 * m + 1] = (float)(wr0 * ci + wi0 * cr);
                 }
                 GatherTap tp;
-                tp.cell = ((jy - ylo) % M) * ROW + (jx % M);
+                tp.cell = place((jy - ylo), jx % M);
                 tp.ant = a;
                 tp.wr = fw[0];
                 tp.wi = fw[1];
@@ -1201,7 +1650,7 @@ static FusedItem build_item(epic_plan p, const std::vector<int> &j0, const std::
     }
     const size_t off = all.size();
     FusedItem fi{};
-    int n_iter = lpt_pack(taps, T, all, J == 4, fi.wave_iter, M == 64 && p->P == 2);
+    int n_iter = lpt_pack(taps, T, all, J == 4, fi.wave_iter, (M == 64 || unfold) && p->P == 2);
     const int rows = J == 4 ? 3 : 1;
     // the kernels load the first entries of every list unconditionally: an
     // item always has at least one (padding) row
@@ -1293,14 +1742,15 @@ static int64_t fused_slots(epic_plan p, int M) {
            : M == 32 ? fused_slots_t<32, 2, false>(p->A) : fused_slots_t<16, 2, false>(p->A);
 }
 
-// Time slices of a paired group's call.  One workgroup fills a CU, so the
-// call takes ceil(workgroups / CUs) rounds of (samples per slice + a start and
+// Time slices of a call of a paired or row-unfolded group.  `slots` workgroups
+// run at once (one paired workgroup fills a CU), so the call takes
+// ceil(workgroups / slots) rounds of (samples per slice + a start and
 // an end that cost about six samples); more than one slice adds the partial
 // image sets' write and read (at about 4 TB/s against 4.5 us per sample) and
 // the reduction's launch.  The cheapest count wins: 1 where the items alone
 // fill whole rounds (128 channels on 256 CUs), 64 for one channel.  Frames
 // need no partial sets, only slices of whole frames.
-static int pair_slices(int64_t n_items, int64_t n_cu, int n_time, int s_max, int64_t part_floats,
+static int pair_slices(int64_t n_items, int64_t slots, int n_time, int s_max, int64_t part_floats,
                        int unit) {
     int best = 1;
     double best_cost = 0.0;
@@ -1308,7 +1758,7 @@ static int pair_slices(int64_t n_items, int64_t n_cu, int n_time, int s_max, int
         const int64_t tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
         const int64_t used = (n_time + tps - 1) / tps;
         if (used != S) continue;
-        const double rounds = std::ceil((double)(n_items * used) / (double)n_cu);
+        const double rounds = std::ceil((double)(n_items * used) / (double)slots);
         const double sets = unit > 1 || S == 1 ? 0.0 : 1.0 + (double)S * part_floats * 8.0 / 18e6;
         const double cost = rounds * ((double)tps + 6.0) + sets;
         if (S == 1 || cost < 0.97 * best_cost) {
@@ -1333,7 +1783,7 @@ static int cu_count() {
 // channel's images get a place in the group's partial image set.
 static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem> &items,
                                hipStream_t s) {
-    const int waves_per_wg = threads_of(g->M) / 64;
+    const int waves_per_wg = threads_of(g) / 64;
     int64_t real = 0;
     for (const FusedItem &fi : items) real += fi.c >= 0;
     const int64_t waves = real * waves_per_wg;
@@ -1351,8 +1801,9 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
         }
     }
     if (p->time_slices > 0) S = p->time_slices;   // the caller's (autotuned) choice
-    g->real_items = real;
-    g->slices = g->kind == 0 ? S : 1;
+    g->slices = g->kind == 0 || (g->kind == 2 && p->time_slices > 0) ? S : 1;
+    g->slots = cu_count();
+    if (g->kind == 2) g->slots *= g->M == 16 ? 12 : 4;   // resident workgroups
     std::vector<int64_t> off(p->C, -1);
     std::vector<GroupChan> chans;
     int64_t n = 0;
@@ -1368,12 +1819,12 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
     }
     g->part_floats = n;
     g->n_chans = (int)chans.size();
-    if (g->kind == 1 && p->time_slices == 0) {
+    if (g->kind != 0 && p->time_slices == 0) {
         // room for the most slices that a call would take (pair_slices), at
         // most 64 and 256 MiB of partial image sets
         const int cap = (int)std::min<int64_t>(64, (int64_t{256} << 20) / (4 * std::max<int64_t>(1, n)));
         for (int nt = 4; nt <= 65536; nt *= 2)
-            g->slices = std::max(g->slices, pair_slices(real, cu_count(), nt, std::max(1, cap), n, 1));
+            g->slices = std::max(g->slices, pair_slices((int64_t)items.size(), g->slots, nt, std::max(1, cap), n, 1));
     }
     epic_status st;
     if ((st = g->chans.alloc(sizeof(GroupChan) * std::max<size_t>(1, chans.size())))) return st;
@@ -1475,23 +1926,6 @@ static epic_status queue_build(epic_plan p, hipStream_t s) {
     return EPIC_OK;
 }
 
-// The butterfly constants of w = exp(+2 pi i n / 128), n < 16 (k_fused_pair).
-static Root root_of(double turns) {
-    const double c = std::cos(2.0 * M_PI * turns), s = std::sin(2.0 * M_PI * turns);
-    if (std::fabs(c) < 1e-9) return Root{s > 0 ? 0x1p40f : -0x1p40f, 0x1p-40f};
-    return Root{(float)(s / c), (float)c};
-}
-static epic_status pair_roots(FusedGroup *g, hipStream_t s) {
-    std::vector<Tw8> r(16);
-    for (int n = 0; n < 16; ++n)
-        r[n] = Tw8{root_of(4 * n / 128.0), root_of(2 * n / 128.0), root_of(n / 128.0),
-                   root_of(n / 128.0 + 0.125)};
-    if (epic_status st = g->roots.alloc(sizeof(Tw8) * r.size())) return st;
-    EPIC_HIP(hipMemcpyAsync(g->roots.p, r.data(), sizeof(Tw8) * r.size(), hipMemcpyHostToDevice, s));
-    EPIC_HIP(hipStreamSynchronize(s));
-    return EPIC_OK;
-}
-
 epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vector<double> &w,
                         hipStream_t s) {
     const int A = p->A, K = p->K;
@@ -1515,7 +1949,7 @@ epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vect
         for (int c = 0; c < p->C; ++c) {
             if (pair_ylo[c] < 0) continue;
             for (int ox = 0; ox < 2; ++ox) {
-                items.push_back(build_item(p, j0, w, c, ox, 0, 64, 512, all, pair_ylo[c]));
+                items.push_back(build_item(p, j0, w, c, ox, 0, 64, 512, all, pair_ylo[c], false, true));
             }
         }
         if (!items.empty()) {
@@ -1523,17 +1957,52 @@ epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vect
             g->M = 64;
             g->kind = 1;
             p->groups.push_back(g);
-            if (epic_status st = pair_roots(g, s)) return st;
             epic_status st = upload_group(p, g, items, all, p->C, s);
             if (st) return st;
         }
+    }
+    // Row-unfolded items: sides 96 and 48 in sub-transforms of a third of the side
+    // (the library's own choice), two feeds, one kernel per element, rows within
+    // half the side, and elements that leave the LDS for it.
+    std::vector<int> rows_ylo(p->C, -1);
+    for (int c = 0; c < p->C; ++c) {
+        const int N = p->ch[c].N;
+        if (queue || p->banded[c] || p->P != 2 || p->J != 1 || A > 2048) continue;
+        if ((N != 96 && N != 48) || p->ch[c].M != N / 3) continue;
+        int lo = 1 << 30, hi = -1;
+        for (int a = 0; a < A; ++a) {
+            const int jy = j0[((size_t)c * A + a) * 2 + 1];
+            lo = std::min(lo, jy);
+            hi = std::max(hi, jy + K - 1);
+        }
+        if (hi - lo < N / 2) rows_ylo[c] = lo;
+    }
+    for (int M : {32, 16}) {
+        std::vector<FusedItem> items;
+        std::vector<uint4> all;
+        auto *g = new FusedGroup();
+        g->M = M;
+        g->kind = 2;
+        const int T = threads_of(g);
+        for (int c = 0; c < p->C; ++c) {
+            if (rows_ylo[c] < 0 || p->ch[c].N != 3 * M) continue;
+            for (int ox = 0; ox < 3; ++ox)
+                items.push_back(build_item(p, j0, w, c, ox, 0, M, T, all, rows_ylo[c], true));
+        }
+        if (items.empty()) {
+            delete g;
+            continue;
+        }
+        p->groups.push_back(g);
+        epic_status st = upload_group(p, g, items, all, p->C, s);
+        if (st) return st;
     }
     for (int M : {64, 32, 16}) {
         std::vector<FusedItem> items;
         std::vector<uint4> all;
         const int T = threads_of(M);
         for (int c = 0; c < p->C; ++c) {
-            if (p->banded[c] || p->ch[c].M != M || pair_ylo[c] >= 0) continue;
+            if (p->banded[c] || p->ch[c].M != M || pair_ylo[c] >= 0 || rows_ylo[c] >= 0) continue;
             const int R = p->ch[c].R;
             for (int oy = 0; oy < R; ++oy)
                 for (int ox = 0; ox < R; ++ox) items.push_back(build_item(p, j0, w, c, ox, oy, M, T, all));
@@ -1635,13 +2104,12 @@ static epic_status launch_pair_fr(const FusedGroup *g, const uint8_t *d_volt, in
     if (st || dry) return st;
     const int unit = FR ? fo.len : 1;
     const int want = FR ? 64 : part && acc ? g->slices : 1;
-    const int S = pair_slices(g->real_items, cu_count(), n_time, want, g->part_floats, unit);
+    const int S = pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit);
     const int tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
     float *sets = !FR && S > 1 ? part : nullptr;
     hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(512), lds, s, g->items.as<FusedItem>(),
                        g->entries.as<uint4>(), d_volt, vstride, A, n_time, acc, autos, fo.len,
-                       fo.out, fo.stride, vb, g->n_items, tps, sets, g->part_floats,
-                       g->roots.as<Tw8>());
+                       fo.out, fo.stride, vb, g->n_items, tps, sets, g->part_floats);
     EPIC_HIP(hipGetLastError());
     if (sets) {
         hipLaunchKernelGGL(k_fused_reduce, dim3(64, g->n_chans), dim3(256), 0, s,
@@ -1671,6 +2139,52 @@ static epic_status launch_pair(const FusedGroup *g, const uint8_t *d_volt, int64
     if (A <= 1024)
         return launch_pair_ar<2, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry, part);
     return launch_pair_ar<4, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry, part);
+}
+
+template <int M, int AR, bool FR>
+static epic_status launch_rows_fr(const FusedGroup *g, const uint8_t *d_volt, int64_t vstride,
+                                  int A, int vb, int n_time, float *acc, int32_t *autos,
+                                  const FrameOut &fo, hipStream_t s, bool dry, float *part,
+                                  bool fixed_slices) {
+    using C = RowsCfg<M>;
+    auto kern = k_fused_rows<M, AR, FR>;
+    epic_status st = lds_ready(reinterpret_cast<const void *>(kern), C::lds(A));
+    if (st || dry) return st;
+    const int unit = FR ? fo.len : 1;
+    const int want = FR ? 64 : part && acc ? g->slices : 1;
+    int S = fixed_slices && !FR
+                ? want
+                : pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit);
+    const int tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
+    S = (n_time + tps - 1) / tps;
+    float *sets = !FR && S > 1 ? part : nullptr;
+    hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(C::T), C::lds(A), s,
+                       g->items.as<FusedItem>(), g->entries.as<uint4>(), d_volt, vstride, A,
+                       n_time, acc, autos, fo.len, fo.out, fo.stride, vb, g->n_items, tps, sets,
+                       g->part_floats);
+    EPIC_HIP(hipGetLastError());
+    if (sets) {
+        hipLaunchKernelGGL(k_fused_reduce, dim3(64, g->n_chans), dim3(256), 0, s,
+                           g->chans.as<GroupChan>(), S, sets, g->part_floats, acc);
+        EPIC_HIP(hipGetLastError());
+    }
+    return EPIC_OK;
+}
+
+template <int M>
+static epic_status launch_rows(const FusedGroup *g, const uint8_t *d_volt, int64_t vstride, int A,
+                               int vb, int n_time, float *acc, int32_t *autos, const FrameOut &fo,
+                               hipStream_t s, bool dry, float *part, bool fixed_slices) {
+    constexpr int T = RowsCfg<M>::T;
+#define EPIC_ROWS(AR)                                                                              \
+    (fo.len ? launch_rows_fr<M, AR, true>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, \
+                                               s, dry, nullptr, fixed_slices)                     \
+            : launch_rows_fr<M, AR, false>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, \
+                                                s, dry, part, fixed_slices))
+    if (A <= T) return EPIC_ROWS(1);
+    if (A <= 2 * T) return EPIC_ROWS(2);
+    return EPIC_ROWS(4);
+#undef EPIC_ROWS
 }
 
 // One persistent launch over the plan's work queue (EPIC_BATCH_QUEUE).
@@ -1738,11 +2252,12 @@ epic_status fused_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, i
     const bool frames = fo.len > 0;
     float *a = acc && !frames ? acc->d_acc.as<float>() : nullptr;
     // The fused kernels add the self-term sums when every group's threads
-    // cover the elements in at most four rounds and no channel is banded;
+    // cover the elements in at most four rounds (one round in row-unfolded
+    // groups, whose registers are full) and no channel is banded;
     // otherwise a separate pass does it for every channel.
     bool in_kernel = p->band.n == 0;
     for (const FusedGroup *g : p->groups)
-        if (p->A > 4 * threads_of(g->M)) in_kernel = false;
+        if (p->A > (g->kind == 2 ? 1 : 4) * threads_of(g)) in_kernel = false;
     int32_t *au = (in_kernel && acc && !frames) ? acc->d_autos.as<int32_t>() : nullptr;
     if (p->band.n) {
         // forks onto the accumulator's own queues; joined back into s below
@@ -1770,7 +2285,11 @@ epic_status fused_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, i
         float *part = (acc && g->slices > 1)
                           ? reinterpret_cast<float *>(acc->d_work.as<char>() + g->work_off)
                           : nullptr;
-        if (g->kind == 1 && p->J == 4) {
+        const bool fixed_slices = p->time_slices > 0;
+        if (g->kind == 2) {
+            if (g->M == 32) st = launch_rows<32>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part, fixed_slices);
+            if (g->M == 16) st = launch_rows<16>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part, fixed_slices);
+        } else if (g->kind == 1 && p->J == 4) {
             st = launch_pair<true>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part);
         } else if (g->kind == 1) {
             st = launch_pair<false>(g, d_volt, vstride, A, vb, n_time, a, au, fo, gs, dry, part);

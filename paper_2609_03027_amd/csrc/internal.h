@@ -100,12 +100,12 @@ struct QueueUnit {
 // A group of fused items that share one sub-transform size M.
 struct FusedGroup {
     int M = 0;
-    int kind = 0;     // 0: one class per item; 1: paired classes (ox, 0) + (ox, 1)
+    int kind = 0;     // 0: one class per item; 1: paired classes (ox, 0) + (ox, 1);
+                      // 2: row-unfolded, every class oy of one ox (M: the y side's)
     int n_items = 0;
-    int64_t real_items = 0;  // without the empty items of the XCD layout
+    int64_t slots = 0;       // kinds 1 and 2: workgroups that run at once
     DevBuf items;     // FusedItem[n_items]
     DevBuf entries;   // uint4 gather entries
-    DevBuf roots;     // kind 1: twiddle constants
     std::vector<FusedItem> host_items;
     // Time slices: with too few waves to fill the chip, each item's samples
     // are split over `slices` workgroups, each storing its Eq. 2 sums to its
