@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "lines.h"
 
 namespace epic {
 
@@ -353,115 +354,113 @@ __global__ __launch_bounds__(1024) void k_fft2d(const float2 *in, float2 *out,
     }
 }
 
-// The same transform for power-of-two sides N <= 128 with N a template
-// constant: the radix schedule (4, 4, ..., then 2 if needed) and every index
-// division become compile-time shifts and masks.  PFN of a thread's PER
-// elements of the next image are prefetched into registers during the
-// transform, the rest loaded at the start of its turn: all of them for
-// N < 128; a quarter at N = 128, where more spill (all 16 need 24 more
-// registers than the 128 a 1024-thread workgroup allows).
-template <int N, int T, int R, int NS>
-__device__ __forceinline__ void p2_pass(float2 *buf, bool along_x, const float2 *__restrict__ tw) {
-    constexpr int pitch = N + 1, nb = N / R, total = N * nb;
-    constexpr int MAXB = (total + T - 1) / T, tstep = N / (NS * R);
-    float2 v[MAXB][R];
-    int ob[MAXB];
-    const int stride = along_x ? 1 : pitch;
-#pragma unroll
-    for (int b = 0; b < MAXB; ++b) {
-        const int u = threadIdx.x + b * T;
-        if (total % T == 0 || u < total) {
-            const int l = u % N, j = u / N, k = j % NS;
-            const int line = along_x ? l * pitch : l;
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                float2 x = buf[line + (j + q * nb) * stride];
-                if (q) x = s_cmul(x, tw[(q * k * tstep) % N]);
-                v[b][q] = x;
-            }
-            s_dft<R>(v[b]);
-            ob[b] = line + ((j / NS) * NS * R + k) * stride;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < MAXB; ++b) {
-        const int u = threadIdx.x + b * T;
-        if (total % T == 0 || u < total) {
-#pragma unroll
-            for (int q = 0; q < R; ++q) buf[ob[b] + q * NS * stride] = v[b][q];
-        }
-    }
-    __syncthreads();
+// The same transform for N = 128, 64, 32 and 16 as N = RA x RB per axis, four
+// register steps with three barriers: along y first, so that a thread's first
+// step takes its inputs straight from HBM (lanes on consecutive columns), then
+// along x, whose last step stores straight to HBM (lanes on RA consecutive
+// frequencies).  A line's step of length RB carries the twiddles exp(+2 pi i p j /
+// N) in its butterflies.  The centring of Eq. 1 needs no factors: rows and columns
+// are read and written half a side further on.  A thread's RA inputs of the next
+// image are loaded once its own first step is done, so the whole next image is in
+// flight during the remaining steps.  Rows of one LDS image lie N + 1 apart.
+//
+// Bound: HBM (one read and one write per image).  64 samples of 32 channels of
+// 128^2 with two feeds, 1.07 GB: 226 us (4.7 TB/s, the rate of a
+// device copy) against 341 with radix-4 passes
+// through LDS (eight passes, seventeen barriers, a quarter of the next image
+// in flight).
+template <int N> struct P2Cfg;
+template <> struct P2Cfg<128> { static constexpr int RA = 16, RB = 8; };
+template <> struct P2Cfg<64> { static constexpr int RA = 8, RB = 8; };
+template <> struct P2Cfg<32> { static constexpr int RA = 8, RB = 4; };
+template <> struct P2Cfg<16> { static constexpr int RA = 4, RB = 4; };
+
+template <int R> __device__ __forceinline__ void p2_dft(float2 *v) {
+    if constexpr (R == 16)
+        dft16(v);
+    else
+        dft<R>(v);
+}
+// Twiddles of the block of frequency p: w = exp(+2 pi i p / N).
+template <int N> __device__ __forceinline__ auto p2_tw(int p) {
+    if constexpr (N == 128) return kRoots.r8[p];
+    else if constexpr (N == 64) return kRoots.r8[2 * p];
+    else if constexpr (N == 32) return kRoots.r4[p];
+    else return kRoots.r4[2 * p];
 }
 
-template <int N, int T, int NS>
-__device__ __forceinline__ void p2_passes(float2 *buf, bool along_x, const float2 *__restrict__ tw) {
-    if constexpr (NS * 4 <= N) {
-        p2_pass<N, T, 4, NS>(buf, along_x, tw);
-        p2_passes<N, T, NS * 4>(buf, along_x, tw);
-    } else if constexpr (NS * 2 <= N) {
-        p2_pass<N, T, 2, NS>(buf, along_x, tw);
-        p2_passes<N, T, NS * 2>(buf, along_x, tw);
-    }
-}
-
-template <int N, int T, int PFN>
-__global__ __launch_bounds__(T) void k_fft2d_p2(const float2 *in, float2 *out,
-                                                   const int32_t *__restrict__ chans, int n_chans,
-                                                   const int64_t *__restrict__ grid_off, int P,
-                                                   int64_t grid_t_stride, int64_t n_img,
-                                                   const float2 *__restrict__ tw) {
-    constexpr int pitch = N + 1, NN = N * N, PER = (NN + T - 1) / T;
+template <int N>
+__global__ __launch_bounds__((N * P2Cfg<N>::RB)) void k_fft2d_p2(
+    const float2 *in, float2 *out, const int32_t *__restrict__ chans, int n_chans,
+    const int64_t *__restrict__ grid_off, int P, int64_t grid_t_stride, int64_t n_img) {
+    constexpr int RA = P2Cfg<N>::RA, RB = P2Cfg<N>::RB, T = N * RB, NB = RA / RB;
+    constexpr int pitch = N + 1, half = N / 2;
     extern __shared__ float2 sbuf[];
-    float2 *twl = sbuf + N * pitch;
     const int tid = threadIdx.x;
-    for (int n = tid; n < N; n += T) twl[n] = tw[n];
     auto base_of = [&](int64_t img) {
         const int p = (int)(img % P);
         const int ci = (int)((img / P) % n_chans);
         const int64_t t = img / ((int64_t)P * n_chans);
-        return t * grid_t_stride + grid_off[chans[ci]] + (int64_t)p * NN;
+        return t * grid_t_stride + grid_off[chans[ci]] + (int64_t)p * N * N;
     };
-    static_assert(PFN >= 0 && PFN <= PER, "prefetch count");
-    float2 pre[PER];
-    // elements k0 .. k1 - 1 of a thread's share of image img
-    auto load = [&](int64_t img, int k0, int k1) {
-        const float2 *src = in + base_of(img);
+    // steps 1 and 2: line (column) tid % N; step 3: line (row) tid % N; the span
+    // index j or block index is tid / N, uniform in a wave for N >= 64
+    const int line = tid % N;
+    const int j = N >= 64 ? __builtin_amdgcn_readfirstlane(tid / N) : tid / N;
+    float2 v[RA];
+    auto load = [&](int64_t img) {
+        const float2 *src = in + base_of(img) + (line ^ half);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * T;
-            if (k >= k0 && k < k1 && (NN % T == 0 || i < NN)) pre[k] = st_load(src + i);
-        }
+        for (int q = 0; q < RA; ++q) v[q] = st_load(src + ((j + RB * q) ^ half) * N);
     };
+    // step 4: block p of row r (+ T / RA per further unit)
+    const int p4 = tid % RA, r4 = tid / RA;
+    const auto tw4 = p2_tw<N>(p4);
     int64_t img = blockIdx.x;
-    if (PFN > 0 && img < n_img) load(img, 0, PFN);
+    if (img < n_img) load(img);
     for (; img < n_img; img += gridDim.x) {
-        if (PFN < PER) load(img, PFN, PER);
+        p2_dft<RA>(v);
+        // X_p[j] of the column to row RB p + j
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * T;
-            if (NN % T == 0 || i < NN) {
-                const int r = i / N, col = i % N;
-                float2 v = pre[k];
-                if ((r + col) & 1) v = make_float2(-v.x, -v.y);
-                sbuf[r * pitch + col] = v;
-            }
+        for (int p = 0; p < RA; ++p) sbuf[(RB * p + j) * pitch + line] = v[p];
+        if (img + gridDim.x < n_img) load(img + gridDim.x);
+        __syncthreads();
+        // row RB p + k: frequency p + RA k along y
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int p = j + RB * b;
+            float2 *s = sbuf + RB * p * pitch + line;
+            float2 x[RB];
+#pragma unroll
+            for (int q = 0; q < RB; ++q) x[q] = s[q * pitch];
+            dft_tw(x, p2_tw<N>(p));
+#pragma unroll
+            for (int q = 0; q < RB; ++q) s[q * pitch] = x[q];
         }
         __syncthreads();
-        if (PFN > 0 && img + gridDim.x < n_img) load(img + gridDim.x, 0, PFN);
-        p2_passes<N, T, 1>(sbuf, true, twl);
-        p2_passes<N, T, 1>(sbuf, false, twl);
+        {
+            float2 *s = sbuf + line * pitch + j;
+            float2 x[RA];
+#pragma unroll
+            for (int q = 0; q < RA; ++q) x[q] = s[RB * q];
+            p2_dft<RA>(x);
+#pragma unroll
+            for (int q = 0; q < RA; ++q) s[RB * q] = x[q];
+        }
+        __syncthreads();
         float2 *dst = out + base_of(img);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * T;
-            if (NN % T == 0 || i < NN) {
-                const int r = i / N, col = i % N;
-                float2 v = sbuf[r * pitch + col];
-                if ((r + col) & 1) v = make_float2(-v.x, -v.y);
-                st_store(dst + i, v);
-            }
+        for (int b = 0; b < NB; ++b) {
+            const int r = r4 + (T / RA) * b;
+            const float2 *s = sbuf + r * pitch + RB * p4;
+            float2 x[RB];
+#pragma unroll
+            for (int q = 0; q < RB; ++q) x[q] = s[q];
+            dft_tw(x, tw4);
+            const int ky = r / RB + RA * (r % RB);
+            float2 *d = dst + (ky ^ half) * N;
+#pragma unroll
+            for (int k = 0; k < RB; ++k) st_store(d + ((p4 + RA * k) ^ half), x[k]);
         }
         __syncthreads();   // every read of this image before the next one's writes
     }
@@ -578,41 +577,41 @@ epic_status staged_image(epic_plan p, const void *d_grid, int n_time, void *d_sk
         const float2 *twd = p->d_twid.as<float2>() + p->twid_off[N];
         if (N <= 128) {
             // whole images in LDS: one read and one write per image;
-            // persistent workgroups, one per CU (the LDS holds one image)
+            // persistent workgroups, as many as the CUs hold at once
             const size_t lds2 = sizeof(float2) * ((size_t)N * (N + 1) + N);
-            epic_status st = lds_ready(reinterpret_cast<const void *>(k_fft2d), lds2);
+            const int64_t n_img = imgs_per_t * n_time;
+            const void *kp2 = N == 128  ? reinterpret_cast<const void *>(k_fft2d_p2<128>)
+                              : N == 64 ? reinterpret_cast<const void *>(k_fft2d_p2<64>)
+                              : N == 32 ? reinterpret_cast<const void *>(k_fft2d_p2<32>)
+                              : N == 16 ? reinterpret_cast<const void *>(k_fft2d_p2<16>)
+                                        : nullptr;
+            const void *kern = kp2 ? kp2 : reinterpret_cast<const void *>(k_fft2d);
+            const int threads = kp2 ? N * (N >= 64 ? 8 : 4) : 1024;
+            epic_status st = lds_ready(kern, lds2);
             if (st) return st;
-            int dev = 0, n_cu = 0;
+            int dev = 0, n_cu = 0, per_cu = 1;
             EPIC_HIP(hipGetDevice(&dev));
             EPIC_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-            const int64_t n_img = imgs_per_t * n_time;
-            const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n_img, n_cu));
-            const void *kp2 = N == 128  ? reinterpret_cast<const void *>(k_fft2d_p2<128, 1024, 4>)
-                              : N == 64 ? reinterpret_cast<const void *>(k_fft2d_p2<64, 1024, 4>)
-                              : N == 32 ? reinterpret_cast<const void *>(k_fft2d_p2<32, 1024, 1>)
-                              : N == 16 ? reinterpret_cast<const void *>(k_fft2d_p2<16, 1024, 1>)
-                                        : nullptr;
+            if (kp2)
+                EPIC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds2));
+            const unsigned blocks = (unsigned)std::max<int64_t>(
+                1, std::min<int64_t>(n_img, (int64_t)n_cu * std::max(1, per_cu)));
+            const float2 *src = static_cast<const float2 *>(d_grid);
+            float2 *dst = static_cast<float2 *>(d_sky);
+            const int64_t *goff = p->d_grid_off.as<int64_t>();
+            const int64_t gts = p->grid_elems_per_t;
+#define EPIC_FFT2D(NN)                                                                         \
+    hipLaunchKernelGGL(k_fft2d_p2<NN>, dim3(blocks), dim3(threads), lds2, s, src, dst, chans,  \
+                       n_chans, goff, p->P, gts, n_img)
             if (kp2) {
-                if ((st = lds_ready(kp2, lds2))) return st;
-                const float2 *gi = static_cast<const float2 *>(d_grid);
-                float2 *go = static_cast<float2 *>(d_sky);
-                const int64_t *goff = p->d_grid_off.as<int64_t>();
-                const int64_t gts = p->grid_elems_per_t;
-                if (N == 128)
-                    hipLaunchKernelGGL((k_fft2d_p2<128, 1024, 4>), dim3(blocks), dim3(1024), lds2, s,
-                                       gi, go, chans, n_chans, goff, p->P, gts, n_img, twd);
-                else if (N == 64)
-                    hipLaunchKernelGGL((k_fft2d_p2<64, 1024, 4>), dim3(blocks), dim3(1024), lds2, s,
-                                       gi, go, chans, n_chans, goff, p->P, gts, n_img, twd);
-                else if (N == 32)
-                    hipLaunchKernelGGL((k_fft2d_p2<32, 1024, 1>), dim3(blocks), dim3(1024), lds2, s,
-                                       gi, go, chans, n_chans, goff, p->P, gts, n_img, twd);
-                else
-                    hipLaunchKernelGGL((k_fft2d_p2<16, 1024, 1>), dim3(blocks), dim3(1024), lds2, s,
-                                       gi, go, chans, n_chans, goff, p->P, gts, n_img, twd);
+                if (N == 128) EPIC_FFT2D(128);
+                else if (N == 64) EPIC_FFT2D(64);
+                else if (N == 32) EPIC_FFT2D(32);
+                else EPIC_FFT2D(16);
                 EPIC_HIP(hipGetLastError());
                 continue;
             }
+#undef EPIC_FFT2D
             hipLaunchKernelGGL(k_fft2d, dim3(blocks), dim3(1024), lds2, s,
                                static_cast<const float2 *>(d_grid), static_cast<float2 *>(d_sky),
                                chans, n_chans, p->d_grid_off.as<int64_t>(), p->P,
