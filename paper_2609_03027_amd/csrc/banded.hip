@@ -27,6 +27,7 @@
 #include <cmath>
 
 #include "internal.h"
+#include "lines.h"
 
 namespace epic {
 
@@ -146,91 +147,6 @@ __device__ float4 *fft_lines(float4 *src, float4 *dst, int N, int pitch, const B
         dst = tmp;
     }
     return src;
-}
-
-// cos(2 pi m / 16), m = 0..15; sin(2 pi m / 16) = cos(2 pi (m - 4) / 16)
-constexpr float kC16[16] = {1.0f,
-                            0.92387953251128674f,
-                            0.70710678118654752f,
-                            0.38268343236508977f,
-                            0.0f,
-                            -0.38268343236508977f,
-                            -0.70710678118654752f,
-                            -0.92387953251128674f,
-                            -1.0f,
-                            -0.92387953251128674f,
-                            -0.70710678118654752f,
-                            -0.38268343236508977f,
-                            0.0f,
-                            0.38268343236508977f,
-                            0.70710678118654752f,
-                            0.92387953251128674f};
-
-// a * exp(+2 pi i m / R), R dividing 16, m known at compile time
-template <int M, int R>
-__device__ __forceinline__ float4 q_rot(float4 a) {
-    constexpr int m = M % R;
-    if constexpr (m == 0) {
-        return a;
-    } else if constexpr (4 * m == R) {
-        return q_mul_i(a);
-    } else if constexpr (2 * m == R) {
-        return make_float4(-a.x, -a.y, -a.z, -a.w);
-    } else if constexpr (4 * m == 3 * R) {
-        return make_float4(a.y, -a.x, a.w, -a.z);
-    } else {
-        constexpr int i16 = m * (16 / R);
-        return q_mul(a, make_float2(kC16[i16], kC16[(i16 + 12) % 16]));
-    }
-}
-
-// 4-point DFT, positive exponent, in place
-__device__ __forceinline__ void dft4(float4 &a, float4 &b, float4 &c, float4 &d) {
-    const float4 t0 = q_add(a, c), t1 = q_sub(a, c);
-    const float4 t2 = q_add(b, d), t3 = q_mul_i(q_sub(b, d));
-    a = q_add(t0, t2);
-    c = q_sub(t0, t2);
-    b = q_add(t1, t3);
-    d = q_sub(t1, t3);
-}
-
-// v[i] *= exp(+2 pi i n2 k1 / R) for i = (R / 4) k1 + n2
-template <int R, int I>
-__device__ __forceinline__ void rot_all(float4 (&v)[R]) {
-    if constexpr (I < R) {
-        constexpr int S = R / 4;
-        v[I] = q_rot<(I % S) * (I / S), R>(v[I]);
-        rot_all<R, I + 1>(v);
-    }
-}
-
-// R-point DFT (R = 8, 16), positive exponent, natural order in, outputs
-// left where the last stage computes them: X[k] in v[dpos<R>(k)].
-// n = (R / 4) n1 + n2, k = k1 + 4 k2; 4-point DFTs over n1, twiddles
-// exp(+2 pi i n2 k1 / R), then (R / 4)-point DFTs over n2 in place.
-template <int R>
-__device__ __forceinline__ constexpr int dpos(int k) {
-    return (R / 4) * (k % 4) + k / 4;
-}
-
-template <int R>
-__device__ __forceinline__ void dft(float4 (&v)[R]) {
-    constexpr int S = R / 4;
-#pragma unroll
-    for (int n2 = 0; n2 < S; ++n2) dft4(v[n2], v[S + n2], v[2 * S + n2], v[3 * S + n2]);
-    // v[S k1 + n2] = Y[n2][k1]
-    rot_all<R, 0>(v);
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) {
-        if constexpr (S == 4) {
-            dft4(v[4 * k1], v[4 * k1 + 1], v[4 * k1 + 2], v[4 * k1 + 3]);
-        } else {
-            const float4 a = v[2 * k1], b = v[2 * k1 + 1];
-            v[2 * k1] = q_add(a, b);
-            v[2 * k1 + 1] = q_sub(a, b);
-        }
-    }
-    // v[S k1 + k2] = X[k1 + 4 k2]
 }
 
 BandRadices radices_of(int N) {
@@ -395,12 +311,13 @@ __global__ __launch_bounds__(BT) void k_band_cols(const BandChan *__restrict__ c
 
 // --------------------------------------------------------- N = R^NP
 // Line transforms of N = R^NP points as NP Stockham passes of radix R, each
-// an R-point DFT in registers.  Thread j of a line takes elements j + qL
-// (L = N / R) in every pass; between passes the line goes through LDS at
-// padded positions p + p / R, which keeps the lanes of a pass in distinct
-// banks.  Pass s (Ns = R^s) multiplies input q by exp(+2 pi i q (j mod Ns)
-// N / (Ns R) / N) and writes output q to (j / Ns) Ns R + j mod Ns + q Ns; the
-// last pass leaves X[j + qL] in registers in natural order.
+// an R-point DFT in registers (both feeds, as two complex arrays).  Thread j of
+// a line takes elements j + qL (L = N / R) in every pass; between passes the line
+// goes through LDS at padded positions p + p / R, which keeps the lanes of a pass
+// in distinct banks.  Pass s (Ns = R^s) multiplies input q by w^q, w = exp(+2 pi i
+// (j mod Ns) / (Ns R)), in its butterflies and writes output q to (j / Ns) Ns R +
+// j mod Ns + q Ns; the last pass leaves X[j + qL] in registers in natural order.
+// A lane's twiddle constants stay in registers.
 template <int R, int NP>
 struct Pw {
     static constexpr int N = NP == 2 ? R * R : R * R * R;
@@ -408,35 +325,69 @@ struct Pw {
     static constexpr int PAD = N + N / R;   // padded line length
 };
 
+struct BandTables {
+    Tw16 r256[16];                          // exp(+2 pi i n / 256)
+    Tw8 r512[64];                           // exp(+2 pi i n / 512)
+};
+constexpr BandTables band_tables() {
+    BandTables t{};
+    for (int n = 0; n < 16; ++n) t.r256[n] = tw16_of(n, 256);
+    for (int n = 0; n < 64; ++n) t.r512[n] = tw8_of(n, 512);
+    return t;
+}
+__constant__ constexpr BandTables kBand = band_tables();
+
+template <int R, int NP> struct PwTw;
+template <> struct PwTw<16, 2> {
+    Tw16 t;
+    __device__ __forceinline__ explicit PwTw(int j) : t(kBand.r256[j]) {}
+    template <int S> __device__ __forceinline__ const Tw16 &pass() const { return t; }
+};
+template <> struct PwTw<8, 2> {
+    Tw8 t;
+    __device__ __forceinline__ explicit PwTw(int j) : t(kRoots.r8[2 * j]) {}
+    template <int S> __device__ __forceinline__ const Tw8 &pass() const { return t; }
+};
+template <> struct PwTw<8, 3> {
+    Tw8 t1, t2;
+    __device__ __forceinline__ explicit PwTw(int j) : t1(kRoots.r8[2 * (j % 8)]), t2(kBand.r512[j]) {}
+    template <int S> __device__ __forceinline__ const Tw8 &pass() const { return S == 1 ? t1 : t2; }
+};
+
+template <int R> __device__ __forceinline__ void pw_dft(float2 *v) {
+    if constexpr (R == 16)
+        dft16(v);
+    else
+        dft<8>(v);
+}
+
 template <int R>
 __device__ __forceinline__ constexpr int padr(int p) {
     return p + p / R;
 }
 
-// Passes 1 .. NP-1 of one line held by thread j (pass 0 already applied to
-// v, in registers, outputs at dpos).  line: this line's LDS base; twl:
-// exp(+2 pi i n / N).  Leaves X[j + qL] in v[dpos<R>(q)].
-template <int R, int NP>
-__device__ __forceinline__ void pw_rest(float4 (&v)[R], float4 *line, int j,
-                                        const float2 *twl) {
-    constexpr int N = Pw<R, NP>::N, L = Pw<R, NP>::L;
-    int Ns = 1;
+// Passes S .. NP-1 of one line held by thread j (pass S - 1 already applied,
+// outputs in x and y).  line: this line's LDS base.
+template <int R, int NP, int P, int S = 1>
+__device__ __forceinline__ void pw_rest(float2 (&x)[R], float2 (&y)[R], float4 *line, int j,
+                                        const PwTw<R, NP> &tw) {
+    constexpr int L = Pw<R, NP>::L, Ns = S == 1 ? 1 : R;   // of pass S - 1
 #pragma unroll
-    for (int s = 1; s < NP; ++s) {
-        // write pass s-1 outputs
+    for (int q = 0; q < R; ++q)
+        line[padr<R>((j / Ns) * Ns * R + j % Ns + q * Ns)] =
+            make_float4(x[q].x, x[q].y, P == 2 ? y[q].x : 0.f, P == 2 ? y[q].y : 0.f);
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < R; ++q)
-            line[padr<R>((j / Ns) * Ns * R + j % Ns + q * Ns)] = v[dpos<R>(q)];
-        __syncthreads();
-        Ns *= R;
-        const int k = j % Ns, tstep = N / (Ns * R);
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const float4 x = line[padr<R>(j + q * L)];
-            v[q] = q ? q_mul(x, twl[(q * k * tstep) % N]) : x;
-        }
-        dft<R>(v);
-        if (s + 1 < NP) __syncthreads();   // every read of this pass before its writes
+    for (int q = 0; q < R; ++q) {
+        const float4 v = line[padr<R>(j + q * L)];
+        x[q] = make_float2(v.x, v.y);
+        y[q] = make_float2(v.z, v.w);
+    }
+    dft_tw(x, tw.template pass<S>());
+    if (P == 2) dft_tw(y, tw.template pass<S>());
+    if constexpr (S + 1 < NP) {
+        __syncthreads();   // every read of this pass before the next one's writes
+        pw_rest<R, NP, P, S + 1>(x, y, line, j, tw);
     }
 }
 
@@ -506,13 +457,11 @@ template <int R, int NP, int P, int VB>
 __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
     const uint8_t *__restrict__ volt, int64_t vstride, const BandChan *__restrict__ chans,
     const BandItem *__restrict__ items, int n_items, int G, int nt, int64_t per_xcd,
-    const uint4 *__restrict__ entries, int A, const float2 *__restrict__ tw,
-    float4 *__restrict__ scratch, int64_t scratch_t) {
+    const uint4 *__restrict__ entries, int A, float4 *__restrict__ scratch, int64_t scratch_t) {
     constexpr int N = Pw<R, NP>::N, L = Pw<R, NP>::L, T = rows_threads<R, NP>();
     constexpr int LP = rows_pitch<R, NP>(), BLR = band_lines(R, NP);
     constexpr int UN = T >= 256 ? 8 : 16;  // gather entries in flight per lane
     extern __shared__ float4 lds[];
-    float2 *twl = reinterpret_cast<float2 *>(lds + BLR * LP);
     // Items come in blocks of G (one channel's bands, padded with empty
     // items); the flat order is block, then sample, then item, so that the
     // workgroups an XCD runs back to back share a sample's voltages and keep
@@ -536,11 +485,6 @@ __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
     const uint8_t *vx = volt + (int64_t)t * vstride + (int64_t)ch.c * P * A * VB;
     const uint4 *ent = entries + it.entry_off;
     const int n_iter = it.n_iter;
-    constexpr int NTW = N / T;
-    static_assert(N % T == 0, "row pass: twiddles fill whole thread strides");
-    float2 twr[NTW];
-#pragma unroll
-    for (int k = 0; k < NTW; ++k) twr[k] = tw[tid + k * T];
     uint4 e[UN];
     uint32_t bx[UN], by[UN];
     if (n_iter > 0) pw_load<UN, P, VB>(e, bx, by, ent, 0, n_iter, T, tid, vx, A, BLR * N);
@@ -553,6 +497,7 @@ __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
         if (i0) pw_load<UN, P, VB>(e, bx, by, ent, i0, n_iter, T, tid, vx, A, BLR * N);
 #pragma unroll
         for (int k = 0; k < UN; ++k) {
+            if (k % 4 == 0 && i0 + k >= n_iter) break;   // uniform; up to three padding taps
             const float wr = __builtin_bit_cast(float, e[k].z);
             const float wi = __builtin_bit_cast(float, e[k].w);
             const int2 x = volt_dec(bx[k], VB);
@@ -569,24 +514,28 @@ __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
             if (e[k].x & 0x80000000u) s = zero;
         }
     }
-    // twiddles (first read after two more barriers) stored once every load
-    // has been waited for
-#pragma unroll
-    for (int k = 0; k < NTW; ++k) twl[tid + k * T] = twr[k];
+    const PwTw<R, NP> tw(j);
     __syncthreads();
     // pass 0 from the gathered band (plain pitch N), then the rest in LDS
-    float4 v[R];
+    float2 x[R], y[R];
 #pragma unroll
-    for (int q = 0; q < R; ++q) v[q] = lds[l * N + j + q * L];
-    dft<R>(v);
+    for (int q = 0; q < R; ++q) {
+        const float4 v = lds[l * N + j + q * L];
+        x[q] = make_float2(v.x, v.y);
+        y[q] = make_float2(v.z, v.w);
+    }
+    pw_dft<R>(x);
+    if (P == 2) pw_dft<R>(y);
     __syncthreads();
-    pw_rest<R, NP>(v, lds + l * LP, j, twl);
+    pw_rest<R, NP, P>(x, y, lds + l * LP, j, tw);
     const int row = ch.row_lo + it.band * BLR + l;
     if (row <= ch.row_hi) {
         float4 *out = scratch + (int64_t)t * scratch_t + ch.scratch_off +
                       (int64_t)(row - ch.row_lo) * N + j;
 #pragma unroll
-        for (int q = 0; q < R; ++q) nt_store(out + q * L, v[dpos<R>(q)]);
+        for (int q = 0; q < R; ++q)
+            nt_store(out + q * L, make_float4(x[q].x, x[q].y, P == 2 ? y[q].x : 0.f,
+                                              P == 2 ? y[q].y : 0.f));
     }
 }
 
@@ -609,15 +558,13 @@ constexpr int cols_waves() {
 template <int R, int NP, int P>
 __global__ __launch_bounds__((cols_threads<R, NP>()))
 __attribute__((amdgpu_waves_per_eu((cols_waves<R, NP>()))))
-void k_band_cols_pw(const BandChan *__restrict__ chans, const float2 *__restrict__ tw,
-                    const float4 *__restrict__ scratch, int64_t scratch_t, int nt,
+void k_band_cols_pw(const BandChan *__restrict__ chans, const float4 *__restrict__ scratch, int64_t scratch_t, int nt,
                     float *__restrict__ acc, float *__restrict__ part, int64_t part_stride,
                     int frame_len, float *__restrict__ frames, int64_t fstride) {
     constexpr int N = Pw<R, NP>::N, L = Pw<R, NP>::L, BC = cols_band<R, NP>();
-    constexpr int T = cols_threads<R, NP>(), LP = cols_pitch<R, NP>();
+    constexpr int LP = cols_pitch<R, NP>();
     constexpr int NPROD = P == 2 ? 4 : 1;
     extern __shared__ float4 lds[];
-    float2 *twl = reinterpret_cast<float2 *>(lds + BC * LP);
     const BandChan ch = chans[blockIdx.y];
     const int S = gridDim.z, slice = blockIdx.z;
     // samples of this workgroup: every S-th from its slice, or (frame mode)
@@ -628,8 +575,7 @@ void k_band_cols_pw(const BandChan *__restrict__ chans, const float2 *__restrict
     const int c0 = blockIdx.x * BC;
     const int tid = threadIdx.x;
     const int l = tid % BC, j = tid / BC;
-    for (int n = tid; n < N; n += T) twl[n] = tw[n];
-    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    const PwTw<R, NP> tw(j);
     // Rows outside the footprint span read a clamped in-range row (no
     // branches around the loads) and are zeroed when used; 32-bit byte
     // offsets from a workgroup-uniform base keep the loads in base + offset
@@ -668,29 +614,33 @@ void k_band_cols_pw(const BandChan *__restrict__ chans, const float2 *__restrict
         for (int k = 0; k < NPROD; ++k) av[q][k] = 0.f;
     float4 *line = lds + l * LP;
     for (int t = t_first; t < t_end; t += t_step) {
-        float4 v[R];
+        float2 x[R], y[R];
         if (!PREF) {
             const char *cur = base + (int64_t)t * tstride;
 #pragma unroll
             for (int q = 0; q < R; ++q) pre[q] = nt_load(cur + off(q));
         }
 #pragma unroll
-        for (int q = 0; q < R; ++q) v[q] = ((live >> q) & 1u) ? pre[q] : zero;
+        for (int q = 0; q < R; ++q) {
+            const bool in = (live >> q) & 1u;
+            x[q] = in ? make_float2(pre[q].x, pre[q].y) : make_float2(0.f, 0.f);
+            y[q] = in ? make_float2(pre[q].z, pre[q].w) : make_float2(0.f, 0.f);
+        }
         if (PREF && t + t_step < t_end) {
             const char *nx = base + (int64_t)(t + t_step) * tstride;
 #pragma unroll
             for (int q = 0; q < R; ++q) pre[q] = nt_load(nx + off(q));
         }
-        dft<R>(v);
-        pw_rest<R, NP>(v, line, j, twl);
+        pw_dft<R>(x);
+        if (P == 2) pw_dft<R>(y);
+        pw_rest<R, NP, P>(x, y, line, j, tw);
 #pragma unroll
         for (int q = 0; q < R; ++q) {
-            const float4 e = v[dpos<R>(q)];
-            av[q][0] = fmaf(e.x, e.x, fmaf(e.y, e.y, av[q][0]));
+            av[q][0] = fmaf(x[q].x, x[q].x, fmaf(x[q].y, x[q].y, av[q][0]));
             if (P == 2) {
-                av[q][1] = fmaf(e.z, e.z, fmaf(e.w, e.w, av[q][1]));
-                av[q][2] = fmaf(e.x, e.z, fmaf(e.y, e.w, av[q][2]));
-                av[q][3] = fmaf(e.y, e.z, fmaf(-e.x, e.w, av[q][3]));
+                av[q][1] = fmaf(y[q].x, y[q].x, fmaf(y[q].y, y[q].y, av[q][1]));
+                av[q][2] = fmaf(x[q].x, y[q].x, fmaf(x[q].y, y[q].y, av[q][2]));
+                av[q][3] = fmaf(x[q].y, y[q].x, fmaf(-x[q].x, y[q].y, av[q][3]));
             }
         }
         __syncthreads();   // every read of the last pass before the next writes
@@ -1377,13 +1327,11 @@ static const void *cols_pw_kernel(int P) {
 }
 template <int R, int NP>
 static size_t rows_pw_lds() {
-    return sizeof(float4) * band_lines(R, NP) * rows_pitch<R, NP>() +
-           sizeof(float2) * Pw<R, NP>::N;
+    return sizeof(float4) * band_lines(R, NP) * rows_pitch<R, NP>();
 }
 template <int R, int NP>
 static size_t cols_pw_lds() {
-    return sizeof(float4) * cols_band<R, NP>() * cols_pitch<R, NP>() +
-           sizeof(float2) * Pw<R, NP>::N;
+    return sizeof(float4) * cols_band<R, NP>() * cols_pitch<R, NP>();
 }
 
 template <int R, int NP>
@@ -1399,7 +1347,6 @@ static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const ui
                              int nt, float4 *scratch, float *part, float *acc,
                              const FrameOut &fo, hipStream_t s) {
     const BandPlan &bp = p->band;
-    const float2 *tw = p->d_twid.as<float2>() + bs.tw_off;
     const BandChan *chans = bp.d_chans.as<BandChan>() + bs.chan_off;
     if (pass == 0) {
         const int64_t vstride = p->vstride();
@@ -1413,11 +1360,11 @@ static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const ui
         if (p->vb == 2)
             hipLaunchKernelGGL((k_band_rows_pw<R, NP, P, 2>), dim3((unsigned)(8 * per_xcd)),
                                dim3(T), lds, s, d_volt, vstride, chans, items, (int)bs.n_items,
-                               bs.G, nt, per_xcd, ent, p->A, tw, scratch, bp.scratch_t);
+                               bs.G, nt, per_xcd, ent, p->A, scratch, bp.scratch_t);
         else
             hipLaunchKernelGGL((k_band_rows_pw<R, NP, P, 1>), dim3((unsigned)(8 * per_xcd)),
                                dim3(T), lds, s, d_volt, vstride, chans, items, (int)bs.n_items,
-                               bs.G, nt, per_xcd, ent, p->A, tw, scratch, bp.scratch_t);
+                               bs.G, nt, per_xcd, ent, p->A, scratch, bp.scratch_t);
         EPIC_HIP(hipGetLastError());
         return EPIC_OK;
     }
@@ -1427,7 +1374,7 @@ static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const ui
     constexpr int BCW = cols_band<R, NP>(), TC = cols_threads<R, NP>();
     const size_t lds = cols_pw_lds<R, NP>();
     hipLaunchKernelGGL((k_band_cols_pw<R, NP, P>), dim3(bs.N / BCW, bs.n, S), dim3(TC), lds, s,
-                       chans, tw, scratch, bp.scratch_t, nt, acc, pp, bs.part_stride, fo.len,
+                       chans, scratch, bp.scratch_t, nt, acc, pp, bs.part_stride, fo.len,
                        fo.out, fo.stride);
     EPIC_HIP(hipGetLastError());
     if (!fo.len && S > 1) {

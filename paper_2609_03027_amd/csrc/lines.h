@@ -199,4 +199,44 @@ __device__ __forceinline__ void dft16(float2 *v) {
     }
 }
 
+// Length 16 with input twiddles w^q: 192 instructions instead of 152 + 60.
+struct Tw16 {
+    Root w8, w4, w2, w2e;                // w^8, w^4, w^2, w^2 exp(2 pi i / 8)
+    Root w1[4];                          // w exp(2 pi i p / 16)
+};
+constexpr Tw16 tw16_of(int n, int L) {   // 16 divides L
+    return Tw16{root_of(8 * n, L), root_of(4 * n, L), root_of(2 * n, L), root_of(2 * n + L / 8, L),
+                {root_of(n, L), root_of(n + L / 16, L), root_of(n + L / 8, L),
+                 root_of(n + 3 * L / 16, L)}};
+}
+__device__ __forceinline__ void dft16_tw(float2 *v, const Tw16 &w) {
+    float2 y[4][4];                     // [j][p]: v[j + 4 q] w^(4 q), the factor w^j left out
+    const Tw4 w44{w.w8, w.w4};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[j][q] = v[j + 4 * q];
+        dft4_tw(y[j], w44);
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {       // input twiddle W = w exp(2 pi i p / 16)
+        float2 a = y[0][p], b = y[1][p], c = y[2][p], d = y[3][p];
+        const Root sq = (p & 1) ? w.w2e : w.w2;    // W^2, for p >= 2 without its factor i
+        if (p < 2) {
+            bfly(a, c, sq);
+            bfly(b, d, sq);
+        } else {
+            bfly_i(a, c, sq);
+            bfly_i(b, d, sq);
+        }
+        bfly(a, b, w.w1[p]);
+        bfly_i(c, d, w.w1[p]);
+        v[p] = a;
+        v[p + 8] = b;
+        v[p + 4] = c;
+        v[p + 12] = d;
+    }
+}
+__device__ __forceinline__ void dft_tw(float2 *v, const Tw16 &w) { dft16_tw(v, w); }
+
 }  // namespace epic
