@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 #include "lines.h"
@@ -59,13 +60,21 @@ __device__ __forceinline__ uint32_t opaque(uint32_t x) {
     return x;
 }
 
-// Raw voltage sample idx (x feed: element a, y feed: A + a) of one (sample,
-// channel) block; VB = bytes per complex sample.  The 32-bit offset lets
-// the load add it to the block's uniform base address directly.
-template <int VB>
-__device__ __forceinline__ uint32_t vraw(const uint8_t *p, uint32_t idx) {
-    if (VB == 2) return *reinterpret_cast<const uint16_t *>(p + 2u * idx);
+// The packed voltages of one element: VB bytes of the x feed, then (P = 2) VB
+// bytes of the y feed.
+template <int P, int VB>
+__device__ __forceinline__ uint32_t pk_load(const uint8_t *p, uint32_t idx) {
+    if constexpr (P * VB == 4) return *reinterpret_cast<const uint32_t *>(p + 4u * idx);
+    if constexpr (P * VB == 2) return *reinterpret_cast<const uint16_t *>(p + 2u * idx);
     return p[idx];
+}
+template <int VB>
+__device__ __forceinline__ int2 pk_x(uint32_t raw) {
+    return volt_dec(raw & (VB == 2 ? 0xffffu : 0xffu), VB);
+}
+template <int VB>
+__device__ __forceinline__ int2 pk_y(uint32_t raw) {
+    return volt_dec(raw >> (8 * VB), VB);
 }
 
 // Streamed scratch accesses: row transforms are written once and read once,
@@ -309,6 +318,58 @@ __global__ __launch_bounds__(BT) void k_band_cols(const BandChan *__restrict__ c
     }
 }
 
+// ------------------------------------------------------ packed voltages
+// A row-pass lane reads the voltages of its taps element by element: from the
+// input layout that is one scattered byte per feed and tap, all over the
+// elements' row.  This pass writes a round's voltages once more, both feeds of an
+// element side by side and the elements ordered by place (rank), so that the
+// elements that meet one band lie in a few cache lines.  One workgroup per
+// (sample, channel); the order is applied in LDS, or where a sample's elements do
+// not fit by scattered stores.  Bound by memory: 4096 elements x 2 feeds x 64
+// channels x 128 samples take 29 us, 134 MB read and written.  (Adding the self-term
+// sums here as well costs more than their own pass, which has fewer atomics.)
+constexpr int PKT = 256;
+constexpr int64_t PK_LDS = 64 << 10;
+
+template <int P, int VB>
+__global__ __launch_bounds__(PKT) void k_band_pack(const uint8_t *__restrict__ volt,
+                                                   int64_t vstride,
+                                                   const BandChan *__restrict__ chans,
+                                                   const int32_t *__restrict__ rank, int A,
+                                                   uint8_t *__restrict__ out, int64_t row,
+                                                   int64_t out_t, int lds) {
+    extern __shared__ uint8_t pk_lds[];
+    using Raw = std::conditional_t<P * VB == 4, uint32_t,
+                                   std::conditional_t<P * VB == 2, uint16_t, uint8_t>>;
+    const int ci = blockIdx.x;
+    const uint8_t *v = volt + (int64_t)blockIdx.y * vstride + (int64_t)chans[ci].c * P * A * VB;
+    uint8_t *dst = out + (int64_t)blockIdx.y * out_t + (int64_t)ci * row;
+    Raw *place = reinterpret_cast<Raw *>(lds ? pk_lds : dst);
+    if (VB == 1 && (A & 3) == 0 && ((uintptr_t)v & 3) == 0) {      // four elements a load
+        for (int a = 4 * threadIdx.x; a < A; a += 4 * PKT) {
+            const uint32_t x = *reinterpret_cast<const uint32_t *>(v + a);
+            const uint32_t y = P == 2 ? *reinterpret_cast<const uint32_t *>(v + A + a) : 0u;
+            const int4 r = *reinterpret_cast<const int4 *>(rank + a);
+            place[r.x] = (Raw)((x & 0xffu) | (y & 0xffu) << 8);
+            place[r.y] = (Raw)((x >> 8 & 0xffu) | (y >> 8 & 0xffu) << 8);
+            place[r.z] = (Raw)((x >> 16 & 0xffu) | (y >> 16 & 0xffu) << 8);
+            place[r.w] = (Raw)((x >> 24) | (y >> 24) << 8);
+        }
+    } else {
+        for (int a = threadIdx.x; a < A; a += PKT) {
+            const uint32_t x = volt_raw(v, a, VB);
+            const uint32_t y = P == 2 ? volt_raw(v, (int64_t)A + a, VB) : 0u;
+            place[rank[a]] = (Raw)(x | y << (8 * (VB & 3)));
+        }
+    }
+    if (!lds) return;
+    __syncthreads();
+    // whole 16-byte groups: row is a multiple of 16 and the LDS is as long
+    const uint4 *src = reinterpret_cast<const uint4 *>(pk_lds);
+    for (int i = threadIdx.x; i < (int)(row / 16); i += PKT)
+        reinterpret_cast<uint4 *>(dst)[i] = src[i];
+}
+
 // --------------------------------------------------------- N = R^NP
 // Line transforms of N = R^NP points as NP Stockham passes of radix R, each
 // an R-point DFT in registers (both feeds, as two complex arrays).  Thread j of
@@ -430,11 +491,11 @@ constexpr int cols_pitch() {
 
 // One batch of UN gather entries of a row-pass lane (iterations past n_iter
 // re-read the last one and become no-op padding entries aimed at LDS slot
-// spare) and the voltage bytes they name.
+// spare) and the packed voltages they name.
 template <int UN, int P, int VB>
-__device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN], uint32_t (&by)[UN],
+__device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN],
                                         const uint4 *__restrict__ ent, int i0, int n_iter, int T,
-                                        int tid, const uint8_t *vx, int A, int spare) {
+                                        int tid, const uint8_t *vx, int spare) {
 #pragma unroll
     for (int k = 0; k < UN; ++k)
         e[k] = ent[(uint32_t)(min(i0 + k, n_iter - 1) * T + tid)];
@@ -443,9 +504,7 @@ __device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN], uint
         if (i0 + k >= n_iter) e[k] = make_uint4(0u, (uint32_t)spare, 0u, 0u);
 #pragma unroll
     for (int k = 0; k < UN; ++k) {
-        const uint32_t a = e[k].x & 0x7fffffffu;
-        bx[k] = vraw<VB>(vx, a);
-        by[k] = P == 2 ? vraw<VB>(vx, (uint32_t)A + a) : 0u;
+        bx[k] = pk_load<P, VB>(vx, e[k].x & 0x7fffffffu);
     }
 }
 
@@ -455,9 +514,10 @@ __device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN], uint
 // the extra registers cost more occupancy than the reuse gained.)
 template <int R, int NP, int P, int VB>
 __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
-    const uint8_t *__restrict__ volt, int64_t vstride, const BandChan *__restrict__ chans,
+    const uint8_t *__restrict__ packed, int64_t pack_t, int64_t pack_row,
+    const BandChan *__restrict__ chans,
     const BandItem *__restrict__ items, int n_items, int G, int nt, int64_t per_xcd,
-    const uint4 *__restrict__ entries, int A, float4 *__restrict__ scratch, int64_t scratch_t) {
+    const uint4 *__restrict__ entries, float4 *__restrict__ scratch, int64_t scratch_t) {
     constexpr int N = Pw<R, NP>::N, L = Pw<R, NP>::L, T = rows_threads<R, NP>();
     constexpr int LP = rows_pitch<R, NP>(), BLR = band_lines(R, NP);
     constexpr int UN = T >= 256 ? 8 : 16;  // gather entries in flight per lane
@@ -482,30 +542,30 @@ __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
     // entries and voltages is loaded before the barrier that publishes the
     // zeroed band, so its two dependent loads overlap the fill and the
     // barrier.
-    const uint8_t *vx = volt + (int64_t)t * vstride + (int64_t)ch.c * P * A * VB;
+    const uint8_t *vx = packed + (int64_t)t * pack_t + (int64_t)it.chan * pack_row;
     const uint4 *ent = entries + it.entry_off;
     const int n_iter = it.n_iter;
     uint4 e[UN];
-    uint32_t bx[UN], by[UN];
-    if (n_iter > 0) pw_load<UN, P, VB>(e, bx, by, ent, 0, n_iter, T, tid, vx, A, BLR * N);
+    uint32_t bx[UN];
+    if (n_iter > 0) pw_load<UN, P, VB>(e, bx, ent, 0, n_iter, T, tid, vx, BLR * N);
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int k = 0; k < BLR * N / T; ++k) lds[tid + k * T] = zero;
     __syncthreads();
     float4 s = zero;
     for (int i0 = 0; i0 < n_iter; i0 += UN) {
-        if (i0) pw_load<UN, P, VB>(e, bx, by, ent, i0, n_iter, T, tid, vx, A, BLR * N);
+        if (i0) pw_load<UN, P, VB>(e, bx, ent, i0, n_iter, T, tid, vx, BLR * N);
 #pragma unroll
         for (int k = 0; k < UN; ++k) {
             if (k % 4 == 0 && i0 + k >= n_iter) break;   // uniform; up to three padding taps
             const float wr = __builtin_bit_cast(float, e[k].z);
             const float wi = __builtin_bit_cast(float, e[k].w);
-            const int2 x = volt_dec(bx[k], VB);
+            const int2 x = pk_x<VB>(bx[k]);
             const float xr = (float)x.x, xi = (float)x.y;
             s.x = fmaf(-wi, xi, fmaf(wr, xr, s.x));
             s.y = fmaf(wi, xr, fmaf(wr, xi, s.y));
             if (P == 2) {
-                const int2 y = volt_dec(by[k], VB);
+                const int2 y = pk_y<VB>(bx[k]);
                 const float yr = (float)y.x, yi = (float)y.y;
                 s.z = fmaf(-wi, yi, fmaf(wr, yr, s.z));
                 s.w = fmaf(wi, yr, fmaf(wr, yi, s.w));
@@ -824,9 +884,10 @@ __device__ __forceinline__ void mf_tap(const uint4 e, const mf_h4 hv, uint32_t *
 
 template <int P, int VB>
 __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
-    const uint8_t *__restrict__ volt, int64_t vstride, const BandChan *__restrict__ chans,
+    const uint8_t *__restrict__ packed, int64_t pack_t, int64_t pack_row,
+    const BandChan *__restrict__ chans,
     const BandItem *__restrict__ items, int n_items, int G, int nt, int64_t per_xcd,
-    const uint4 *__restrict__ entries, const int32_t *__restrict__ ants, int A,
+    const uint4 *__restrict__ entries, const int32_t *__restrict__ ants,
     uint2 *__restrict__ scratch, int64_t scratch_t, const MfConst *__restrict__ mfc) {
     constexpr int N = 256, T = 128;
     // the two planes of BL * N FP16 cells (+ the spare slot), then the
@@ -851,23 +912,20 @@ __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
     const MfConst k = mf_consts(mfc, lane);
     const int32_t *al = ants + it.ant_off;
     const uint4 *ent = entries + it.entry_off;
-    const uint8_t *vc = volt + (int64_t)ch.c * P * A * VB;
+    const uint8_t *vc = packed + (int64_t)it.chan * pack_row;
     // the voltages of the elements that meet this band are decoded once per
     // sample into LDS as FP16 (exact for 4- and 8-bit integers; the entries
     // index this list); a lane's first two elements are read one sample
     // ahead, the rest when staged
-    uint32_t ai[2] = {0u, 0u}, rx[2] = {0u, 0u}, ry[2] = {0u, 0u};
+    uint32_t ai[2] = {0u, 0u}, rx[2] = {0u, 0u};
 #pragma unroll
     for (int j = 0; j < 2; ++j)
         if (tid + j * T < it.n_ants) ai[j] = (uint32_t)al[tid + j * T];
     auto fetch = [&](int t) {
-        const uint8_t *vx = vc + (int64_t)t * vstride;
+        const uint8_t *vx = vc + (int64_t)t * pack_t;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            if (tid + j * T < it.n_ants) {
-                rx[j] = vraw<VB>(vx, ai[j]);
-                if (P == 2) ry[j] = vraw<VB>(vx, (uint32_t)A + ai[j]);
-            }
+            if (tid + j * T < it.n_ants) rx[j] = pk_load<P, VB>(vx, ai[j]);
     };
     if (t0 < t1) fetch(t0);
     // a lane list of at most MF_UN entries is read once for all the samples;
@@ -885,17 +943,16 @@ __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             if (tid + j * T < it.n_ants) {
-                const int2 x = volt_dec(rx[j], VB);
-                const int2 y = P == 2 ? volt_dec(ry[j], VB) : make_int2(0, 0);
+                const int2 x = pk_x<VB>(rx[j]);
+                const int2 y = P == 2 ? pk_y<VB>(rx[j]) : make_int2(0, 0);
                 vst[tid + j * T] = mf_h4{(_Float16)x.x, (_Float16)x.y, (_Float16)y.x, (_Float16)y.y};
             }
         if (it.n_ants > 2 * T) {
-            const uint8_t *vx = vc + (int64_t)t * vstride;
+            const uint8_t *vx = vc + (int64_t)t * pack_t;
             for (int i = tid + 2 * T; i < it.n_ants; i += T) {
-                const uint32_t an = (uint32_t)al[i];
-                const int2 x = volt_dec(vraw<VB>(vx, an), VB);
-                const int2 y = P == 2 ? volt_dec(vraw<VB>(vx, (uint32_t)A + an), VB)
-                                      : make_int2(0, 0);
+                const uint32_t raw = pk_load<P, VB>(vx, (uint32_t)al[i]);
+                const int2 x = pk_x<VB>(raw);
+                const int2 y = P == 2 ? pk_y<VB>(raw) : make_int2(0, 0);
                 vst[i] = mf_h4{(_Float16)x.x, (_Float16)x.y, (_Float16)y.x, (_Float16)y.y};
             }
         }
@@ -1059,11 +1116,15 @@ static epic_status band_items(epic_plan p, const std::vector<int> &j0,
                               const std::vector<double> &w, const BandChan &b, int chan_index,
                               int bl, int T, int G, std::vector<BandItem> &items,
                               std::vector<uint4> &all, bool compact,
-                              std::vector<int32_t> &ants) {
+                              std::vector<int32_t> &ants, const std::vector<int32_t> &rank,
+                              const std::vector<int32_t> &by_rank) {
     const int A = p->A, K = p->K, N = b.N, c = b.c;
     const int n_bands = (b.row_hi - b.row_lo + 1 + bl - 1) / bl;
     std::vector<std::vector<GatherTap>> per(n_bands);
-    for (int a = 0; a < A; ++a) {
+    for (int i = 0; i < A; ++i) {
+        // a cell's taps in the packed order; the FP16 path, whose half-precision
+        // sums depend on it, keeps the element order
+        const int a = compact ? i : by_rank[i];
         const int jx0 = j0[((size_t)c * A + a) * 2], jy0 = j0[((size_t)c * A + a) * 2 + 1];
         for (int dy = 0; dy < K; ++dy)
             for (int dx = 0; dx < K; ++dx) {
@@ -1073,7 +1134,7 @@ static epic_status band_items(epic_plan p, const std::vector<int> &j0,
                 const double sg = ((row + col) & 1) ? -1.0 : 1.0;
                 GatherTap tp{};
                 tp.cell = (row - r0) * N + col;
-                tp.ant = a;
+                tp.ant = rank[a];
                 tp.wr = (float)(sg * w[wi]);
                 tp.wi = (float)(-sg * w[wi + 1]);
                 per[band].push_back(tp);
@@ -1137,6 +1198,22 @@ epic_status banded_build(epic_plan p, const std::vector<int> &j0, const std::vec
     // the FP16 four-step row pass keeps BL-line bands; the FP32 row pass
     // takes band_lines(R, NP)
     const bool mf = p->precision == EPIC_F16_MFMA;
+    // the packed order: strips of four grid rows of the middle banded channel,
+    // along each strip by column
+    std::vector<int32_t> rank(p->A), by_rank(p->A);
+    {
+        int mid = 0, seen = 0;
+        const int n_banded = (int)std::count(p->banded.begin(), p->banded.end(), (char)1);
+        for (int c = 0; c < p->C; ++c)
+            if (p->banded[c] && seen++ == n_banded / 2) mid = c;
+        for (int a = 0; a < p->A; ++a) by_rank[a] = a;
+        auto at = [&](int a, int k) { return j0[((size_t)mid * p->A + a) * 2 + k]; };
+        std::stable_sort(by_rank.begin(), by_rank.end(), [&](int x, int y) {
+            const int sx = at(x, 1) / 4, sy = at(y, 1) / 4;
+            return sx != sy ? sx < sy : at(x, 0) < at(y, 0);
+        });
+        for (int i = 0; i < p->A; ++i) rank[by_rank[i]] = i;
+    }
     int64_t off = 0;
     for (int N : sides) {
         BandSize bs;
@@ -1187,7 +1264,7 @@ epic_status banded_build(epic_plan p, const std::vector<int> &j0, const std::vec
                 band_items(p, j0, w, b, (int)(bp.host.size() - bs.chan_off),
                            mf ? BL : band_lines(bs.R, bs.NP),
                            (mf ? BL : band_lines(bs.R, bs.NP)) * (bs.N / bs.R),
-                           bs.G, items, all, compact, ants);
+                           bs.G, items, all, compact, ants, rank, by_rank);
             bp.host.push_back(b);
             bs.max_bands = std::max(bs.max_bands, (hi - lo + 1 + BL - 1) / BL);
             ++bs.n;
@@ -1288,6 +1365,13 @@ epic_status banded_build(epic_plan p, const std::vector<int> &j0, const std::vec
         }
     }
     epic_status st;
+    bp.pack_row = ((int64_t)p->A * p->vb * p->P + 15) / 16 * 16;
+    bp.pack_off = (bp.scratch_bytes + bp.part_bytes + 255) / 256 * 256;
+    for (const BandSize &bs : bp.sizes)
+        if (bs.R) bp.pack_bytes = 2 * (int64_t)bp.t_chunk * bp.n * bp.pack_row;
+    if ((st = bp.d_rank.alloc(sizeof(int32_t) * rank.size()))) return st;
+    EPIC_HIP(hipMemcpyAsync(bp.d_rank.p, rank.data(), sizeof(int32_t) * rank.size(),
+                            hipMemcpyHostToDevice, s));
     if ((st = bp.d_chans.alloc(sizeof(BandChan) * bp.host.size()))) return st;
     EPIC_HIP(hipMemcpyAsync(bp.d_chans.p, bp.host.data(), sizeof(BandChan) * bp.host.size(),
                             hipMemcpyHostToDevice, s));
@@ -1343,13 +1427,12 @@ static epic_status ready_pw(int P) {
 }
 
 template <int R, int NP, int P>
-static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const uint8_t *d_volt,
+static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const uint8_t *packed,
                              int nt, float4 *scratch, float *part, float *acc,
                              const FrameOut &fo, hipStream_t s) {
     const BandPlan &bp = p->band;
     const BandChan *chans = bp.d_chans.as<BandChan>() + bs.chan_off;
     if (pass == 0) {
-        const int64_t vstride = p->vstride();
         const int64_t total = bs.n_items * nt;
         const int64_t per_xcd = (total + 7) / 8;
         if (8 * per_xcd > 0x7fffffff) return fail(EPIC_ERR_ARG, "banded path: grid too large");
@@ -1359,12 +1442,12 @@ static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const ui
         const uint4 *ent = bp.d_entries.as<uint4>();
         if (p->vb == 2)
             hipLaunchKernelGGL((k_band_rows_pw<R, NP, P, 2>), dim3((unsigned)(8 * per_xcd)),
-                               dim3(T), lds, s, d_volt, vstride, chans, items, (int)bs.n_items,
-                               bs.G, nt, per_xcd, ent, p->A, scratch, bp.scratch_t);
+                               dim3(T), lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
+                               (int)bs.n_items, bs.G, nt, per_xcd, ent, scratch, bp.scratch_t);
         else
             hipLaunchKernelGGL((k_band_rows_pw<R, NP, P, 1>), dim3((unsigned)(8 * per_xcd)),
-                               dim3(T), lds, s, d_volt, vstride, chans, items, (int)bs.n_items,
-                               bs.G, nt, per_xcd, ent, p->A, scratch, bp.scratch_t);
+                               dim3(T), lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
+                               (int)bs.n_items, bs.G, nt, per_xcd, ent, scratch, bp.scratch_t);
         EPIC_HIP(hipGetLastError());
         return EPIC_OK;
     }
@@ -1408,7 +1491,7 @@ static epic_status ready_mf(int P) {
 // FP16 four-step MFMA passes (256 x 256 channels of EPIC_F16_MFMA plans):
 // same grids and items as launch_pw<16, 2, P>; the scratch holds FP16 cells.
 template <int P>
-static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const uint8_t *d_volt,
+static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const uint8_t *packed,
                              int nt, float4 *scratch, float *part, float *acc, hipStream_t s) {
     const BandPlan &bp = p->band;
     const BandChan *chans = bp.d_chans.as<BandChan>() + bs.chan_off;
@@ -1425,13 +1508,13 @@ static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const ui
             return fail(EPIC_ERR_UNSUPPORTED, "FP16 four-step: more than 4096 elements in a band");
         if (p->vb == 2)
             hipLaunchKernelGGL((k_band_rows_mf<P, 2>), dim3((unsigned)(8 * per_xcd)), dim3(128),
-                               lds, s, d_volt, p->vstride(), chans, items, (int)bs.n_items,
-                               bs.G, nt, per_xcd, ent, ants, p->A, sc, bp.scratch_t,
+                               lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
+                               (int)bs.n_items, bs.G, nt, per_xcd, ent, ants, sc, bp.scratch_t,
                                bp.d_mf.as<MfConst>());
         else
             hipLaunchKernelGGL((k_band_rows_mf<P, 1>), dim3((unsigned)(8 * per_xcd)), dim3(128),
-                               lds, s, d_volt, p->vstride(), chans, items, (int)bs.n_items,
-                               bs.G, nt, per_xcd, ent, ants, p->A, sc, bp.scratch_t,
+                               lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
+                               (int)bs.n_items, bs.G, nt, per_xcd, ent, ants, sc, bp.scratch_t,
                                bp.d_mf.as<MfConst>());
         EPIC_HIP(hipGetLastError());
         return EPIC_OK;
@@ -1453,14 +1536,45 @@ static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const ui
 
 template <int P>
 static epic_status launch_pw_any(epic_plan p, const BandSize &bs, int pass,
-                                 const uint8_t *d_volt, int nt, float4 *scratch, float *part,
+                                 const uint8_t *packed, int nt, float4 *scratch, float *part,
                                  float *acc, const FrameOut &fo, hipStream_t s) {
+    packed += bs.chan_off * p->band.pack_row;
     if (p->precision == EPIC_F16_MFMA)
-        return launch_mf<P>(p, bs, pass, d_volt, nt, scratch, part, acc, s);
-    if (bs.R == 16) return launch_pw<16, 2, P>(p, bs, pass, d_volt, nt, scratch, part, acc, fo, s);
+        return launch_mf<P>(p, bs, pass, packed, nt, scratch, part, acc, s);
+    if (bs.R == 16) return launch_pw<16, 2, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
     if (bs.R == 8 && bs.NP == 2)
-        return launch_pw<8, 2, P>(p, bs, pass, d_volt, nt, scratch, part, acc, fo, s);
-    return launch_pw<8, 3, P>(p, bs, pass, d_volt, nt, scratch, part, acc, fo, s);
+        return launch_pw<8, 2, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
+    return launch_pw<8, 3, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
+}
+
+static const void *pack_kernel(int P, int vb) {
+    if (P == 2)
+        return vb == 2 ? reinterpret_cast<const void *>(k_band_pack<2, 2>)
+                       : reinterpret_cast<const void *>(k_band_pack<2, 1>);
+    return vb == 2 ? reinterpret_cast<const void *>(k_band_pack<1, 2>)
+                   : reinterpret_cast<const void *>(k_band_pack<1, 1>);
+}
+
+// Pack nt samples of every banded channel.
+static epic_status launch_pack(epic_plan p, const uint8_t *d_volt, int nt, uint8_t *packed,
+                               hipStream_t s) {
+    const BandPlan &bp = p->band;
+    const int use = bp.pack_row <= PK_LDS ? 1 : 0;
+    const size_t lds = use ? (size_t)bp.pack_row : 0;
+    const dim3 grid((unsigned)bp.n, (unsigned)nt);
+    const int64_t vs = p->vstride(), pt = bp.n * bp.pack_row;
+#define EPIC_PACK(PP, VV)                                                                       \
+    hipLaunchKernelGGL((k_band_pack<PP, VV>), grid, dim3(PKT), lds, s, d_volt, vs,               \
+                       bp.d_chans.as<BandChan>(), bp.d_rank.as<int32_t>(), p->A, packed,        \
+                       bp.pack_row, pt, use)
+    if (p->P == 2) {
+        if (p->vb == 2) EPIC_PACK(2, 2); else EPIC_PACK(2, 1);
+    } else {
+        if (p->vb == 2) EPIC_PACK(1, 2); else EPIC_PACK(1, 1);
+    }
+#undef EPIC_PACK
+    EPIC_HIP(hipGetLastError());
+    return EPIC_OK;
 }
 
 static epic_status launch_generic(epic_plan p, const BandSize &bs, int pass,
@@ -1552,8 +1666,10 @@ epic_status banded_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, 
         }
         if (st) return st;
     }
+    if (bp.pack_bytes)
+        if (epic_status st = lds_ready(pack_kernel(p->P, p->vb), 0)) return st;
     if (dry) return EPIC_OK;
-    if (!acc->d_work.p || acc->d_work.bytes < (size_t)(bp.scratch_bytes + bp.part_bytes) ||
+    if (!acc->d_work.p || acc->d_work.bytes < (size_t)(bp.pack_off + bp.pack_bytes) ||
         !acc->band_q[0])
         return fail(EPIC_ERR_ARG, "accumulator has no scratch for the banded path");
     float *part = reinterpret_cast<float *>(acc->d_work.as<char>() + bp.scratch_bytes);
@@ -1586,13 +1702,18 @@ epic_status banded_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, 
         float4 *scratch = reinterpret_cast<float4 *>(acc->d_work.as<char>() + b * half);
         const uint8_t *v = d_volt + (int64_t)t0 * p->vstride();
         if (split && k >= 2) EPIC_HIP(hipStreamWaitEvent(q_rows, ev[3 + b], 0));
+        // (the packed half is free as well: its row pass ended before the column
+        // pass that the event stands for)
+        uint8_t *packed = acc->d_work.as<uint8_t>() + bp.pack_off + b * (bp.pack_bytes / 2);
+        if (bp.pack_bytes) st = launch_pack(p, v, nt, packed, q_rows);
         for (int pass = 0; pass < 2 && !st; ++pass) {
             const hipStream_t qs = pass ? q_cols : q_rows;
             if (split && pass == 1) EPIC_HIP(hipStreamWaitEvent(q_cols, ev[1 + b], 0));
             for (const BandSize &bs : bp.sizes) {
                 if (bs.R)
-                    st = p->P == 2 ? launch_pw_any<2>(p, bs, pass, v, nt, scratch, part, a, fr, qs)
-                                   : launch_pw_any<1>(p, bs, pass, v, nt, scratch, part, a, fr, qs);
+                    st = p->P == 2
+                             ? launch_pw_any<2>(p, bs, pass, packed, nt, scratch, part, a, fr, qs)
+                             : launch_pw_any<1>(p, bs, pass, packed, nt, scratch, part, a, fr, qs);
                 else
                     st = launch_generic(p, bs, pass, chans, v, nt, scratch, a, qs);
                 if (st) break;

@@ -183,6 +183,11 @@ struct BandPlan {
     int elem_bytes = 16;     // bytes per scratch cell: float4, or 8 (FP16 four-step)
     int64_t scratch_bytes = 0;  // two halves of row transforms
     int64_t part_bytes = 0;     // column-pass partial sums, after the scratch
+    // packed voltages of a round (two halves), after the partial sums: per sample
+    // and channel pack_row bytes, both feeds of an element together, the elements
+    // in the order d_rank gives (by place, so that a band's lie together)
+    int64_t pack_off = 0, pack_row = 0, pack_bytes = 0;
+    DevBuf d_rank;           // int32 [A]: place of element a in the packed order
     std::vector<BandSize> sizes;
     std::vector<BandChan> host;
     DevBuf d_chans;          // BandChan[n]

@@ -302,7 +302,7 @@ epic_status plan_build(epic_plan p, hipStream_t s) {
     if (p->precision == EPIC_F32 || p->band_only()) {
         if ((st = fused_build(p, j0, w, s))) return st;
         if ((st = banded_build(p, j0, w, s))) return st;
-        p->work_bytes = p->band.scratch_bytes + p->band.part_bytes;
+        p->work_bytes = p->band.pack_off + p->band.pack_bytes;
         fused_assign_work(p);
     } else if (p->precision == EPIC_FIXED16) {
         if ((st = fixed_build(p, j0, w, s))) return st;
@@ -324,7 +324,7 @@ epic_status plan_build(epic_plan p, hipStream_t s) {
         p->bytes_plan += (int64_t)(g->items.bytes + g->entries.bytes + g->chans.bytes);
     p->bytes_plan += (int64_t)(p->band.d_chans.bytes + p->band.d_items.bytes +
                                p->band.d_entries.bytes + p->band.d_mf.bytes +
-                               p->band.d_ants.bytes);
+                               p->band.d_ants.bytes + p->band.d_rank.bytes);
     for (epic::DevBuf *b : {&p->gemm.a_hi, &p->gemm.a_lo, &p->gemm.d_blk_off,
                             &p->gemm.d_scale, &p->gemm.d_inv_s2, &p->fixed.items,
                             &p->fixed.entries, &p->fixed.tw, &p->sep.fy, &p->sep.fx,
