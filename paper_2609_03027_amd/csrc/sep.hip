@@ -9,8 +9,10 @@
 // for 8 Na^2 N + 8 N^2 Na real flops per image (aperture pruning) instead of
 // 8 N^2 A for the direct beam matrix.  Both steps are complex products done
 // as real MFMA products on block matrices:
-//   step 1:  [Hr; Hi] rows (re/im, feed, u) = [[Gr, -Gi], [Gi, Gr]] [Far^T; Fai^T]
-//   step 2:  [Er; Ei] rows (ky, re/im)      = [[Far, -Fai], [Fai, Far]] [Hr; Hi]
+//   step 1:  [Hr; Hi] rows (feed, u) = [[Gr, -Gi], [Gi, Gr]] [Far^T; Fai^T]
+//   step 2:  [Er; Ei] rows (ky, re/im) = [[Far, -Fai], [Fai, Far]] [Hr; Hi]
+// with the contracted index ordered (v, re/im) and (u, re/im): a cell's re and im
+// are one word in LDS, stored and read together,
 // with FP16 (or BF16 hi + lo) operands and FP32 accumulation.  The grid is
 // formed per sample in LDS from plan-time lane lists (each lane owns whole
 // cells, no atomics), H passes through LDS, E never leaves registers: the
@@ -18,10 +20,11 @@
 //
 // Scaling: every operand that is rounded to 16 bits is first multiplied by an
 // exact power of two chosen at plan time from worst-case bounds, 2^-sa for the
-// grid (folded into the gather weights) and 2^-sb for H, so no value leaves
-// the 16-bit range; the products are multiplied back by 2^(2 (sa + sb)).
+// grid (folded into the gather weights) and 2^-sb for H (folded into step 1's
+// Fa), so no value leaves the 16-bit range; the products are multiplied back by 2^(2 (sa + sb)).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -62,6 +65,15 @@ __device__ __forceinline__ uint16_t bf16_bits(float x) {
     u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even
     return (uint16_t)(u >> 16);
 }
+// Two values rounded to 16 bits, the first in the low half.
+__device__ __forceinline__ uint32_t f16_pair(float lo, float hi) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
+}
+__device__ __forceinline__ uint32_t halves_swapped(uint32_t x) {
+    return __builtin_amdgcn_alignbit(x, x, 16);
+}
 __device__ __forceinline__ float bf16_val(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // MFMA 16 x 16 x 32 (FP16 or BF16 operands, FP32 accumulate).  Operand
@@ -93,7 +105,7 @@ struct SepItem {
 
 struct SepArgs {
     const SepItem *items;
-    const uint4 *entries;   // [iter][lane] {ant | last << 31, cell u NA + v, wr, wi}
+    const uint4 *entries;   // [iter][lane] {16 ant | last << 31, cell u GPW + v, wr, wi}
     const uint4 *fy;        // step-2 A fragments [hl][N/8 row blocks][KS][64]
     const uint4 *fx;        // step-1 B fragments [hl][N/32 tiles][2][KS][64]
     const uint8_t *volt;
@@ -101,19 +113,25 @@ struct SepArgs {
     int A, vb, C, n_time, tps, S;
     int64_t per_xcd, total;
     int astage;             // elements the LDS stage holds (>= A)
-    float h_scale;          // 2^-sb applied to H before rounding
     float out_scale;        // 2^(2 (sa + sb)) applied to the products
     float *acc;             // sums (when S == 1)
     float *part;            // slice partial sums [S][image_floats] (when S > 1)
     int64_t part_stride;
 };
 
-// One workgroup per (time slice, channel, W-column kx tile).  Step 1: wave w
+// One workgroup per (time slice, channel, W-column kx tile).  A sample's products
+// keep the matrix cores busy for 3100 clocks of a CU, its vector instructions (the
+// Eq. 2 sums, gather and conversions) the SIMDs for about 3000 and its operands the
+// LDS for 2800; what it takes, 6500, is how far these overlap on two waves a SIMD.
+// Hence the words of re and im (half the scattered stores and step-1 reads), the
+// two waves of a SIMD at different phases and the products' higher priority:
+// 128 channels of 256 elements, 250 samples, took 1055 us before and 845 us now
+// (the phases 5 %, the priority 5 %).  Step 1: wave w
 // owns CBW adjacent 16-column blocks of the tile (group w % NCG) and every
-// (NW / NCG)-th row block (re/im, feed, u) from w / NCG; step 2: wave w owns
-// the row blocks (ky, re/im) (w / HXG) RB2W .. + RB2W - 1 and the columns
-// (feed, kx) of column-pair group w % HXG.  HL = 1 (FP16) or 2 (BF16 hi + lo: products hi hi + hi lo +
-// lo hi).
+// (NW / NCG)-th row block (feed, 16 u; re and im) from w / NCG; step 2: wave w
+// owns the row blocks (ky, re/im) (w / HXG) RB2W .. + RB2W - 1 and the columns
+// (feed, kx) of column-pair group w % HXG.  HL = 1 (FP16) or 2 (BF16 hi + lo:
+// products hi hi + hi lo + lo hi).
 template <int DT, int N, int NA, bool PIPE>
 __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
     using SH = SepShape<DT, N>;
@@ -124,16 +142,16 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
     constexpr int NCB = W / 16;              // step-1 column blocks of a tile
     constexpr int CBW = SH::CBW;             // of which a wave takes CBW adjacent ones
     constexpr int NCG = NCB / CBW;           // column-block groups
-    constexpr int NRB1 = NA / 4;             // step-1 row blocks (4 NA rows)
+    constexpr int NRB1 = NA / 8;             // step-1 row blocks (feed, 16 u), re and im each
     constexpr int RSTEP = NW / NCG;          // waves sharing a column-block group
     constexpr int RB1W = NRB1 / RSTEP;       // step-1 row blocks per wave
     constexpr int RB2 = N / 8;               // step-2 row blocks (2 N rows)
     constexpr int HXG = SH::HXG;             // step-2 column-pair groups
     constexpr int RB2W = RB2 * HXG / NW;     // step-2 row blocks per wave
     constexpr int NHX = W / 16 / HXG;        // step-2 column blocks per feed and wave
-    constexpr int GP = NA + 8;               // grid row pitch (16-bit values)
-    constexpr int GPLANE = NA * GP;          // one (feed, re/im) plane
-    constexpr int KP = 2 * NA + 8;           // H column pitch
+    constexpr int GP = 2 * NA + 8;           // grid row pitch (16-bit values; re, im of v)
+    constexpr int GPLANE = NA * GP;          // one feed's plane
+    constexpr int KP = 2 * NA + 8;           // H column pitch (re, im of u)
     static_assert(RB2W >= 1 && RB1W >= 1 && NCB % CBW == 0 && NW % NCG == 0 && NHX >= 1 &&
                       NW % HXG == 0, "grid sides");
     // PIPE: two of each buffer, one sample's gather, another's step 1 and a
@@ -141,8 +159,8 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
     constexpr int NB = PIPE ? 2 : 1;
     extern __shared__ float4 smem[];
     float4 *stage0 = smem;                                                  // [NB][astage]
-    uint16_t *grid0 = reinterpret_cast<uint16_t *>(smem + NB * a.astage);   // [NB][HL][2][2][NA][GP]
-    uint16_t *hbuf0 = grid0 + NB * HL * 4 * GPLANE;                         // [NB][HL][2 W][KP]
+    uint16_t *grid0 = reinterpret_cast<uint16_t *>(smem + NB * a.astage);   // [NB][HL][2][NA][GP]
+    uint16_t *hbuf0 = grid0 + NB * HL * 2 * GPLANE;                         // [NB][HL][2 W][KP]
 
     const int64_t L = (int64_t)(blockIdx.x % 8) * a.per_xcd + blockIdx.x / 8;
     if (L >= a.total) return;
@@ -176,7 +194,8 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
             for (int s = 0; s < KS; ++s)
                 a2[h][r][s] = a.fy[(((int64_t)h * RB2 + rg2 * RB2W + r) * KS + s) * 64 + lane];
     }
-    for (int i = tid; i < NB * HL * 4 * GPLANE; i += T) grid0[i] = 0;   // cells without taps stay 0
+    for (int i = tid; i < NB * HL * 2 * (GPLANE + W * KP); i += T)
+        grid0[i] = 0;                        // cells without taps stay 0; H before the first sample
 
     float sum[RB2W][NHX][2][4];
 #pragma unroll
@@ -209,7 +228,7 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
     }
     // phases of one sample: stage its voltages, gather its grid, step 1
     // (grid -> H), step 2 (H -> E, products into the sums)
-    auto stage_t = [&](int t, float4 *stage) {
+    auto stage_t = [&](int t, float4 *stage) __attribute__((always_inline)) {
         const uint8_t *vt = vc + (int64_t)t * a.vstride;
         if (tid < a.A) {
             const int2 x = volt_dec(rx, a.vb), y = volt_dec(ry, a.vb);
@@ -220,126 +239,154 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
             stage[e] = make_float4((float)x.x, (float)x.y, (float)y.x, (float)y.y);
         }
     };
-    auto fetch_t = [&](int t) {   // the raw bytes of sample t, into rx / ry
+    auto fetch_t = [&](int t) __attribute__((always_inline)) {   // the raw bytes of sample t, into rx / ry
         if (t < t_stop && tid < a.A) {
             const uint8_t *vn = vc + (int64_t)t * a.vstride;
             rx = volt_raw(vn, tid, a.vb);
             ry = volt_raw(vn, (int64_t)a.A + tid, a.vb);
         }
     };
-    // gather: each lane sums whole cells, conj(W) 2^-sa E, and writes each
-    // once; entries are loaded eight at a time (indices clamped into the
-    // list, the surplus not applied) so a lane waits for one L2 round trip
-    // per eight entries
-    auto gather_t = [&](const float4 *stage, uint16_t *grid, const EntryBatch<GB> hb) {
-        {
-            float sxr = 0.f, sxi = 0.f, syr = 0.f, syi = 0.f;
-            for (int i0 = 0; i0 < it.n_iter; i0 += GB) {
-                uint4 eb[GB];
-                if (held) {
+    // gather: each lane sums whole cells, conj(W) 2^-sa E; entries are loaded
+    // eight at a time (indices clamped into the list) so a lane waits for one
+    // L2 round trip per eight.  Every entry stores its cell's sum so far, re and
+    // im of a feed as one word: a cell's last one stands, and nothing branches
+    // (padding entries go to a word of row 0's pad).
+    float sxr = 0.f, sxi = 0.f, syr = 0.f, syi = 0.f;
+    auto taps = [&](const float4 *stage, uint16_t *grid, const EntryBatch<GB> &eb, auto n) __attribute__((always_inline)) {
+        uint32_t *g32 = reinterpret_cast<uint32_t *>(grid);
+        const char *st = reinterpret_cast<const char *>(stage);
+        constexpr int VG = HL == 1 ? 4 : 2;        // voltages in flight
+        float4 v[VG];
 #pragma unroll
-                    for (int k = 0; k < GB; ++k) eb[k] = hb.e[k];
-                } else {
+        for (int k = 0; k < n; ++k) {
+            if (k % VG == 0) {
 #pragma unroll
-                    for (int k = 0; k < GB; ++k)
-                        eb[k] = ent[(int64_t)min(i0 + k, it.n_iter - 1) * T];
+                for (int q = 0; q < VG && k + q < n; ++q)
+                    v[q] = *reinterpret_cast<const float4 *>(st + (eb.e[k + q].x & 0x7FFFFFFFu));
+            }
+            const uint4 e = eb.e[k];
+            const float wr = __uint_as_float(e.z), wi = __uint_as_float(e.w);
+            sxr = fmaf(-wi, v[k % VG].y, fmaf(wr, v[k % VG].x, sxr));
+            sxi = fmaf(wi, v[k % VG].x, fmaf(wr, v[k % VG].y, sxi));
+            syr = fmaf(-wi, v[k % VG].w, fmaf(wr, v[k % VG].z, syr));
+            syi = fmaf(wi, v[k % VG].z, fmaf(wr, v[k % VG].w, syi));
+            if constexpr (HL == 1) {
+                g32[e.y] = f16_pair(sxr, sxi);
+                g32[GPLANE / 2 + e.y] = f16_pair(syr, syi);
+            } else {
+                const float val[2][2] = {{sxr, sxi}, {syr, syi}};
+#pragma unroll
+                for (int pl = 0; pl < 2; ++pl) {
+                    const uint32_t h0 = bf16_bits(val[pl][0]), h1 = bf16_bits(val[pl][1]);
+                    const uint32_t l0 = bf16_bits(val[pl][0] - bf16_val(h0));
+                    const uint32_t l1 = bf16_bits(val[pl][1] - bf16_val(h1));
+                    g32[pl * (GPLANE / 2) + e.y] = h0 | h1 << 16;
+                    g32[(2 + pl) * (GPLANE / 2) + e.y] = l0 | l1 << 16;
                 }
+            }
+            // the cell's last entry clears the sums (as bits: selects become
+            // branches here)
+            const uint32_t keep = ~(uint32_t)((int)e.x >> 31);
+            sxr = __uint_as_float(__float_as_uint(sxr) & keep);
+            sxi = __uint_as_float(__float_as_uint(sxi) & keep);
+            syr = __uint_as_float(__float_as_uint(syr) & keep);
+            syi = __uint_as_float(__float_as_uint(syi) & keep);
+        }
+    };
+    auto gather_t = [&](const float4 *stage, uint16_t *grid, const EntryBatch<GB> hb) __attribute__((always_inline)) {
+        sxr = sxi = syr = syi = 0.f;
+        for (int i0 = 0; i0 < it.n_iter; i0 += GB) {
+            EntryBatch<GB> eb;
+            if (held) {
+                eb = hb;
+            } else {
 #pragma unroll
-                for (int k = 0; k < GB; ++k) {
-                    if (i0 + k >= it.n_iter) break;
-                    const uint4 e = eb[k];
-                    const float4 v = stage[e.x & 0x7FFFFFFFu];
-                    const float wr = __uint_as_float(e.z), wi = __uint_as_float(e.w);
-                    sxr = fmaf(-wi, v.y, fmaf(wr, v.x, sxr));
-                    sxi = fmaf(wi, v.x, fmaf(wr, v.y, sxi));
-                    syr = fmaf(-wi, v.w, fmaf(wr, v.z, syr));
-                    syi = fmaf(wi, v.z, fmaf(wr, v.w, syi));
-                    if (e.x >> 31) {
-                        const int u = (int)e.y / NA, vv = (int)e.y % NA;
-                        const int o = u * GP + vv;
-                        const float val[4] = {sxr, sxi, syr, syi};   // planes (feed, re/im)
-#pragma unroll
-                        for (int pl = 0; pl < 4; ++pl) {
-                            if (HL == 1) {
-                                grid[pl * GPLANE + o] = f16_bits(val[pl]);
-                            } else {
-                                const uint16_t hi = bf16_bits(val[pl]);
-                                grid[pl * GPLANE + o] = hi;
-                                grid[(4 + pl) * GPLANE + o] = bf16_bits(val[pl] - bf16_val(hi));
-                            }
-                        }
-                        sxr = sxi = syr = syi = 0.f;
-                    }
-                }
+                for (int k = 0; k < GB; ++k)
+                    eb.e[k] = ent[(uint32_t)(min(i0 + k, it.n_iter - 1) * T)];
+            }
+            switch (min(GB, it.n_iter - i0)) {       // uniform
+            case 1: taps(stage, grid, eb, std::integral_constant<int, 1>()); break;
+            case 2: taps(stage, grid, eb, std::integral_constant<int, 2>()); break;
+            case 3: taps(stage, grid, eb, std::integral_constant<int, 3>()); break;
+            case 4: taps(stage, grid, eb, std::integral_constant<int, 4>()); break;
+            case 5: taps(stage, grid, eb, std::integral_constant<int, 5>()); break;
+            case 6: taps(stage, grid, eb, std::integral_constant<int, 6>()); break;
+            case 7: taps(stage, grid, eb, std::integral_constant<int, 7>()); break;
+            default: taps(stage, grid, eb, std::integral_constant<int, 8>()); break;
             }
         }
     };
-    auto step1_t = [&](const uint16_t *grid, uint16_t *hbuf) {
-        // step 1: this wave's row blocks (ri, p, u) of its column blocks
+    auto step1_t = [&](const uint16_t *grid, uint16_t *hbuf) __attribute__((always_inline)) {
+        // step 1: this wave's row blocks (p, u) of its column blocks; the words
+        // (Gr, Gi) read once give the rows of Hr as (Gr, -Gi) and of Hi as (Gi, Gr)
 #pragma unroll
         for (int r = 0; r < RB1W; ++r) {
-            const int rb = rw1 + r * RSTEP;            // 0 .. NA / 4 - 1
+            const int rb = rw1 + r * RSTEP;            // 0 .. NA / 8 - 1
             const int ublk = rb % (NA / 16);
-            const int p = (rb / (NA / 16)) & 1;
-            const int ri = rb / (NA / 8);
+            const int p = rb / (NA / 16);
             const int u = ublk * 16 + col;
             uint4 ga[HL][KS];
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const int k = 32 * s + 8 * g;
-                const int rip = k / NA, v0 = k % NA;
-                // plane: real part where ri == rip, imaginary part otherwise
-                const int reim = (ri == rip) ? 0 : 1;
-                const bool neg = (ri == 0 && rip == 1);
+            for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int h = 0; h < HL; ++h) {
-                    uint4 x = *reinterpret_cast<const uint4 *>(
-                        grid + (h * 4 + p * 2 + reim) * GPLANE + u * GP + v0);
-                    if (neg) {
-                        x.x ^= 0x80008000u;
-                        x.y ^= 0x80008000u;
-                        x.z ^= 0x80008000u;
-                        x.w ^= 0x80008000u;
+                for (int h = 0; h < HL; ++h)
+                    ga[h][s] = *reinterpret_cast<const uint4 *>(
+                        grid + (h * 2 + p) * GPLANE + u * GP + 32 * s + 8 * g);
+            sf4 d[CBW][2];
+#pragma unroll
+            for (int ri = 0; ri < 2; ++ri) {
+                // ri 0 first: the words turned into their other form in place
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+#pragma unroll
+                    for (int h = 0; h < HL; ++h) {
+                        uint4 &x = ga[h][s];
+                        x.x = ri ? halves_swapped(x.x ^ 0x80000000u) : x.x ^ 0x80000000u;
+                        x.y = ri ? halves_swapped(x.y ^ 0x80000000u) : x.y ^ 0x80000000u;
+                        x.z = ri ? halves_swapped(x.z ^ 0x80000000u) : x.z ^ 0x80000000u;
+                        x.w = ri ? halves_swapped(x.w ^ 0x80000000u) : x.w ^ 0x80000000u;
                     }
-                    ga[h][s] = x;
-                }
+#pragma unroll
+                for (int c = 0; c < CBW; ++c) d[c][ri] = sf4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+#pragma unroll
+                    for (int c = 0; c < CBW; ++c) {
+                        d[c][ri] = mma<DT>(ga[0][s], b1[0][c][s], d[c][ri]);
+                        if (HL == 2) {
+                            d[c][ri] = mma<DT>(ga[0][s], b1[HL - 1][c][s], d[c][ri]);
+                            d[c][ri] = mma<DT>(ga[HL - 1][s], b1[0][c][s], d[c][ri]);
+                        }
+                    }
             }
 #pragma unroll
             for (int c = 0; c < CBW; ++c) {
-                sf4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    d = mma<DT>(ga[0][s], b1[0][c][s], d);
-                    if (HL == 2) {
-                        d = mma<DT>(ga[0][s], b1[HL - 1][c][s], d);
-                        d = mma<DT>(ga[HL - 1][s], b1[0][c][s], d);
-                    }
-                }
                 // rows 4 g + i: u = ublk 16 + 4 g + i of column kx = cb 16 + col
                 const int n2 = p * W + (cg1 * CBW + c) * 16 + col;
-                const int k2 = ri * NA + ublk * 16 + 4 * g;
-                uint16_t hv[HL][4];
+                const int k2 = 2 * (ublk * 16 + 4 * g);
+                uint32_t hv[HL][4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float x = d[i] * a.h_scale;
-                    if (HL == 1) {
-                        hv[0][i] = f16_bits(x);
+                    const float x = d[c][0][i], y = d[c][1][i];
+                    if constexpr (HL == 1) {
+                        hv[0][i] = f16_pair(x, y);
                     } else {
-                        hv[0][i] = bf16_bits(x);
-                        hv[HL - 1][i] = bf16_bits(x - bf16_val(hv[0][i]));
+                        const uint32_t hx = bf16_bits(x), hy = bf16_bits(y);
+                        const uint32_t lx = bf16_bits(x - bf16_val(hx)), ly = bf16_bits(y - bf16_val(hy));
+                        hv[0][i] = hx | hy << 16;
+                        hv[HL - 1][i] = lx | ly << 16;
                     }
                 }
 #pragma unroll
                 for (int h = 0; h < HL; ++h)
-                    *reinterpret_cast<uint2 *>(hbuf + (h * 2 * W + n2) * KP + k2) =
-                        make_uint2((uint32_t)hv[h][0] | (uint32_t)hv[h][1] << 16,
-                                   (uint32_t)hv[h][2] | (uint32_t)hv[h][3] << 16);
+                    *reinterpret_cast<uint4 *>(hbuf + (h * 2 * W + n2) * KP + k2) =
+                        make_uint4(hv[h][0], hv[h][1], hv[h][2], hv[h][3]);
             }
             // one row block's operands live at a time
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto step2_t = [&](const uint16_t *hbuf) {
+    auto step2_t = [&](const uint16_t *hbuf) __attribute__((always_inline)) {
         // step 2: rows (ky, re/im) of this wave; columns (feed, kx) of the tile;
         // x and y blocks of one kx block give both feeds of the same pixels
 #pragma unroll
@@ -356,18 +403,19 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
                         bq[h][s] = *reinterpret_cast<const uint4 *>(
                             hbuf + (h * 2 * W + n2) * KP + 32 * s + 8 * g);
 #pragma unroll
-                for (int r = 0; r < RB2W; ++r) {
-                    sf4 x = {0.f, 0.f, 0.f, 0.f};
+                for (int r = 0; r < RB2W; ++r) d[p][r] = sf4{0.f, 0.f, 0.f, 0.f};
+                // row blocks in turn: no product waits for the one before
 #pragma unroll
-                    for (int s = 0; s < KS; ++s) {
+                for (int s = 0; s < KS; ++s)
+#pragma unroll
+                    for (int r = 0; r < RB2W; ++r) {
+                        sf4 &x = d[p][r];
                         x = mma<DT>(a2[0][r][s], bq[0][s], x);
                         if (HL == 2) {
                             x = mma<DT>(a2[0][r][s], bq[HL - 1][s], x);
                             x = mma<DT>(a2[HL - 1][r][s], bq[0][s], x);
                         }
                     }
-                    d[p][r] = x;
-                }
             }
             // lane rows 4 g + i: pixel q = i / 2 (ky = row block 8 + 2 g + q), re / im
 #pragma unroll
@@ -399,25 +447,42 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
             // the next sample's staging is ordered after step 2 by its barrier
         }
     } else if (t_begin < t_stop) {
-        // iteration i: stage i + 1, gather i, step 1 of i - 1, step 2 of i - 2
-        // (sample j uses buffer (j - t_begin) & 1 of each kind; one barrier
-        // per iteration orders every write before the next iteration's read
-        // and every read before the write two iterations on)
+        // between two barriers: stage i + 1, gather i, step 1 of i - 1, step 2 of
+        // i - 2 (sample j uses buffer (j - t_begin) & 1 of each kind; the barrier
+        // orders every write before the next interval's read and every read
+        // before the write two intervals on).  The phases are of different
+        // samples, so their order in an interval is free: half the waves do step 2
+        // first, that is, pass the barrier before it instead of after, so that
+        // the two waves of a SIMD are not at the same phase.  Step 2 also
+        // runs on the two intervals before the first sample, on zeros: a branch
+        // around it would copy the sums.
+        auto run = [&](auto ahead) __attribute__((always_inline)) {
+            for (int i = t_begin; i < t_stop + (ahead ? 1 : 2); ++i) {
+                const int b = (i - t_begin) & 1;
+                if (i + 1 < t_stop) {
+                    stage_t(i + 1, stage0 + (b ^ 1) * a.astage);
+                    fetch_t(i + 2);
+                }
+                if (i < t_stop) gather_t(stage0 + b * a.astage, grid0 + b * (HL * 2 * GPLANE), eh);
+                // the products go first where both waves of a SIMD can issue
+                __builtin_amdgcn_s_setprio(1);
+                if (i - 1 >= t_begin && i - 1 < t_stop)
+                    step1_t(grid0 + (b ^ 1) * (HL * 2 * GPLANE),
+                            hbuf0 + (b ^ 1) * (HL * 2 * W * KP));
+                __builtin_amdgcn_s_setprio(0);
+                if (ahead) __syncthreads();
+                __builtin_amdgcn_s_setprio(1);
+                step2_t(hbuf0 + (ahead ? b ^ 1 : b) * (HL * 2 * W * KP));
+                __builtin_amdgcn_s_setprio(0);
+                if (!ahead) __syncthreads();
+            }
+            if (ahead) __syncthreads();
+        };
         stage_t(t_begin, stage0);
         fetch_t(t_begin + 1);
         __syncthreads();
-        for (int i = t_begin; i < t_stop + 2; ++i) {
-            const int b = (i - t_begin) & 1;
-            if (i + 1 < t_stop) {
-                stage_t(i + 1, stage0 + (b ^ 1) * a.astage);
-                fetch_t(i + 2);
-            }
-            if (i < t_stop) gather_t(stage0 + b * a.astage, grid0 + b * (HL * 4 * GPLANE), eh);
-            if (i - 1 >= t_begin && i - 1 < t_stop)
-                step1_t(grid0 + (b ^ 1) * (HL * 4 * GPLANE), hbuf0 + (b ^ 1) * (HL * 2 * W * KP));
-            if (i - 2 >= t_begin) step2_t(hbuf0 + b * (HL * 2 * W * KP));
-            __syncthreads();
-        }
+        if (wave < NW / 2) run(std::false_type());
+        else run(std::true_type());
     }
     if (t_begin >= t_stop) return;
     const int64_t plane = (int64_t)N * N;
@@ -498,7 +563,7 @@ size_t sep_lds(int dt, int N, int NA, int A, bool pipe) {
     const size_t hl = dt == EPIC_BF16X2_MFMA ? 2 : 1;
     const size_t W = (size_t)sep_dims(dt, N).W;
     return (pipe ? 2 : 1) *
-           (sizeof(float4) * (size_t)sep_astage(A) + sizeof(uint16_t) * hl * 4 * NA * (NA + 8) +
+           (sizeof(float4) * (size_t)sep_astage(A) + sizeof(uint16_t) * hl * 2 * NA * (2 * NA + 8) +
             sizeof(uint16_t) * hl * 2 * W * (2 * NA + 8));
 }
 
@@ -612,6 +677,14 @@ epic_status sep_build(epic_plan p, const std::vector<int> &j0, const std::vector
         items[c].c = c;
         items[c].entry_off = (int64_t)all.size();
         items[c].n_iter = lpt_pack(taps, dims.T, all);
+        // as the kernel reads them: byte offset of the staged voltage, word of the
+        // cell in rows of NA + 4 words; padding aims at row 0's pad
+        for (size_t e = (size_t)items[c].entry_off; e < all.size(); ++e) {
+            uint4 &t = all[e];
+            const bool pad = t.x == 0u && t.y == 0u && t.z == 0u && t.w == 0u;
+            t.x = (t.x & 0x80000000u) | (t.x & 0x7FFFFFFFu) * (uint32_t)sizeof(float4);
+            t.y = pad ? (uint32_t)NA : t.y / NA * (NA + 4) + t.y % NA;
+        }
         items[c].img_off = p->ch[c].img_off;
     }
 
@@ -628,21 +701,22 @@ epic_status sep_build(epic_plan p, const std::vector<int> &j0, const std::vector
         im = std::sin(ang);
     };
     const int KS = 2 * NA / 32, RB2 = N / 8;
-    // step-2 A: row r = (ky, ri) = (r / 2, r % 2), k = (ri', u) = (k / NA, k % NA)
+    // step-2 A: row r = (ky, ri) = (r / 2, r % 2), k = (u, ri') = (k / 2, k % 2)
     std::vector<uint16_t> fyh((size_t)RB2 * KS * 64 * 8), fyl(fyh.size());
     for (int rb = 0; rb < RB2; ++rb)
         for (int st = 0; st < KS; ++st)
             for (int l = 0; l < 64; ++l)
                 for (int j = 0; j < 8; ++j) {
                     const int r = rb * 16 + (l & 15), k = 32 * st + 8 * (l >> 4) + j;
-                    const int ky = r / 2, ri = r % 2, rip = k / NA, u = k % NA;
+                    const int ky = r / 2, ri = r % 2, rip = k % 2, u = k / 2;
                     double fr, fi;
                     fa(ky, u, fr, fi);
                     const double v = (ri == 0) ? (rip == 0 ? fr : -fi) : (rip == 0 ? fi : fr);
                     put16(dt, fyh, fyl, (((size_t)rb * KS + st) * 64 + l) * 8 + j, v);
                 }
-    // step-1 B: 16-column block cb, column kx = 16 cb + l % 16, k = (ri', v):
-    // Re / Im Fa[kx][v]
+    // step-1 B: 16-column block cb, column kx = 16 cb + l % 16, k = (v, ri'):
+    // 2^-sb Re / Im Fa[kx][v] (exact: sb is at most 6, and what is not zero of Fa is at
+    // least sin(2 pi / 128) > 2^-5)
     std::vector<uint16_t> fxh((size_t)(N / 16) * KS * 64 * 8), fxl(fxh.size());
     for (int cb = 0; cb < N / 16; ++cb)
         for (int st = 0; st < KS; ++st)
@@ -650,9 +724,9 @@ epic_status sep_build(epic_plan p, const std::vector<int> &j0, const std::vector
                 for (int j = 0; j < 8; ++j) {
                     const int kx = cb * 16 + (l & 15), k = 32 * st + 8 * (l >> 4) + j;
                     double fr, fi;
-                    fa(kx, k % NA, fr, fi);
+                    fa(kx, k / 2, fr, fi);
                     put16(dt, fxh, fxl, (((size_t)cb * KS + st) * 64 + l) * 8 + j,
-                          k / NA == 0 ? fr : fi);
+                          std::ldexp(k % 2 == 0 ? fr : fi, -sb));
                 }
     std::vector<uint16_t> fy, fx;
     fy.insert(fy.end(), fyh.begin(), fyh.end());
@@ -717,7 +791,6 @@ epic_status sep_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, int
     a.total = (int64_t)a.S * p->C * NT;
     a.per_xcd = (a.total + 7) / 8;
     if (8 * a.per_xcd > 0x7fffffff) return fail(EPIC_ERR_ARG, "separable DFT-GEMM: grid too large");
-    a.h_scale = (float)std::ldexp(1.0, -sp.sb);
     a.out_scale = (float)std::ldexp(1.0, 2 * (sp.sa + sp.sb));
     a.acc = acc->d_acc.as<float>();
     a.part = a.S > 1 ? acc->d_work.as<float>() : nullptr;
