@@ -1668,7 +1668,10 @@ static int cu_count() {
 
 // Time slices of a one-class-per-item group: at least enough workgroups for
 // about four waves per SIMD (1024 SIMDs), then the fewest slices (at most 16)
-// whose last round of resident workgroups is at least 90 % full; each
+// whose last round of resident workgroups is at least 90 % full; where one or a
+// few small grids leave the chip idle, up to 64 slices (one 32 x 32 channel of 1000
+// samples: 144 us with 16, 51 us with 64; not for 64 x 64 items, whose slices cost
+// more than they save: two 128 x 128 channels of 250 samples 110 and 140 us); each
 // channel's images get a place in the group's partial image set.
 static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem> &items,
                                hipStream_t s) {
@@ -1676,7 +1679,8 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
     int64_t real = 0;
     for (const FusedItem &fi : items) real += fi.c >= 0;
     const int64_t waves = real * waves_per_wg;
-    int S = (int)std::max<int64_t>(1, std::min<int64_t>(16, (4096 + waves - 1) / std::max<int64_t>(1, waves)));
+    const int cap = g->M == 64 ? 16 : 64;
+    int S = (int)std::max<int64_t>(1, std::min<int64_t>(cap, (4096 + waves - 1) / std::max<int64_t>(1, waves)));
     const int64_t slots = g->kind == 0 ? fused_slots(p, g->M) : 0;
     if (slots > 0) {
         // workgroups launched = padded items x slices
