@@ -194,8 +194,10 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
             for (int s = 0; s < KS; ++s)
                 a2[h][r][s] = a.fy[(((int64_t)h * RB2 + rg2 * RB2W + r) * KS + s) * 64 + lane];
     }
-    for (int i = tid; i < NB * HL * 2 * (GPLANE + W * KP); i += T)
-        grid0[i] = 0;                        // cells without taps stay 0; H before the first sample
+    // cells without taps stay 0; H before the first sample
+    static_assert(GPLANE % 8 == 0 && KP % 8 == 0, "16-byte words");
+    for (int i = tid; i < NB * HL * (GPLANE + W * KP) / 4; i += T)
+        reinterpret_cast<uint4 *>(grid0)[i] = make_uint4(0u, 0u, 0u, 0u);
 
     float sum[RB2W][NHX][2][4];
 #pragma unroll
