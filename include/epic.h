@@ -84,7 +84,7 @@ typedef enum {
                                w_n = rint(2^ts exp(+2 pi i n / 64)), ts = twiddle bits - 1,
                                rsh(x, k) = (x + 2^(k-1)) >> k (round half up), b_s bit s of
                                the stage mask (bits 0-5 rows, 6-11 columns).  Products of
-                               the integer sky values are summed exactly (FP64) and added
+                               the integer sky values are summed exactly (64 bits) and added
                                to the FP32 accumulator once per call, times
                                2^(2 (halving stages + sg - sw)).  Every grid side must be 64;
                                not with EPIC_JONES, frames or the banded path.  The staged
@@ -207,7 +207,8 @@ typedef struct {
                                     each sample is packed, samples may be spaced further
                                     apart (a ring with headers, a larger capture buffer) */
     int32_t time_slices;         /* fused size groups of one class per item (paired groups
-                                    take none) and the work queue (EPIC_F32): split
+                                    take the library's choice for 0 and none otherwise)
+                                    and the work queue (EPIC_F32): split
                                     each call's samples into this many time slices, each
                                     summed into its own partial image set and reduced in
                                     slice order (deterministic for a given value; other
