@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "roots.h"
+
 namespace epic {
 
 // ---------------------------------------------------------------- complex
@@ -49,9 +51,6 @@ template <> __device__ __forceinline__ void dft<8>(float2 *v) {
 // u = (1 + i t) b and four for a +- c u, so the transform with its seven
 // twiddles costs 72 instructions instead of 52 + 28.  c = 0 is held as c =
 // 2^-40, t = 2^40, whose products are exact.
-struct Root {
-    float t, c;
-};
 struct Tw8 {
     Root w4, w2, w1, w1e;                // w^4, w^2, w, w exp(2 pi i / 8)
 };
@@ -117,30 +116,6 @@ __device__ __forceinline__ void dft4_tw(float2 *v, const Tw4 &w) {
     v[2] = t;
 }
 
-// The constants of w = exp(+2 pi i n / L), from compile-time series (|x| <= pi,
-// 2 n / L <= 1 / 2: exact to FP64 rounding before they are rounded to FP32).
-constexpr double kPi = 3.14159265358979323846;
-constexpr double series_cos(double x) {
-    double s = 1.0, t = 1.0;
-    for (int k = 1; k < 24; ++k) {
-        t *= -x * x / ((2.0 * k - 1.0) * (2.0 * k));
-        s += t;
-    }
-    return s;
-}
-constexpr double series_sin(double x) {
-    double s = x, t = x;
-    for (int k = 1; k < 24; ++k) {
-        t *= -x * x / ((2.0 * k) * (2.0 * k + 1.0));
-        s += t;
-    }
-    return s;
-}
-constexpr Root root_of(int n, int L) {
-    if (4 * n == L) return Root{0x1p40f, 0x1p-40f};
-    const double x = 2.0 * kPi * n / L, c = series_cos(x);
-    return Root{(float)(series_sin(x) / c), (float)c};
-}
 constexpr Tw8 tw8_of(int n, int L) {     // 8 divides L
     return Tw8{root_of(4 * n, L), root_of(2 * n, L), root_of(n, L), root_of(n + L / 8, L)};
 }
