@@ -50,7 +50,9 @@ template <> __device__ __forceinline__ void dft<8>(float2 *v) {
 // follows it.  With w = c (1 + i t), a +- w b takes two fused multiply-adds for
 // u = (1 + i t) b and four for a +- c u, so the transform with its seven
 // twiddles costs 72 instructions instead of 52 + 28.  c = 0 is held as c =
-// 2^-40, t = 2^40, whose products are exact.
+// 2^-40, t = 2^40, whose products are exact.  |t b| may pass FP32's range where
+// |b| does not (above 2^87): for transforms whose |E|^2 has to fit FP32, not for
+// those that return E.
 struct Tw8 {
     Root w4, w2, w1, w1e;                // w^4, w^2, w, w exp(2 pi i / 8)
 };
@@ -152,7 +154,22 @@ template <> struct LineTw<16> {
 __device__ __forceinline__ void dft_tw(float2 *v, const Tw8 &w) { dft8_tw(v, w); }
 __device__ __forceinline__ void dft_tw(float2 *v, const Tw4 &w) { dft4_tw(v, w); }
 
-// Length 16 as 4 x 4, constant twiddles in the second step's butterflies.
+// a exp(+2 pi i m / 16), m a constant after unrolling
+__device__ __forceinline__ float2 rot16(float2 a, int m) {
+    constexpr float c1 = 0.92387953251128675613f, s1 = 0.38268343236508977173f;
+    constexpr float h = 0.70710678118654752440f;
+    switch (m) {
+        case 0: return a;
+        case 1: return cmul(a, make_float2(c1, s1));
+        case 2: return cmul(a, make_float2(h, h));
+        case 3: return cmul(a, make_float2(s1, c1));
+        case 4: return mul_i(a);
+        case 6: return cmul(a, make_float2(-h, h));
+        default: return cmul(a, make_float2(-c1, -s1));     // 9
+    }
+}
+
+// Length 16 as 4 x 4, constant twiddles between the steps.
 __device__ __forceinline__ void dft16(float2 *v) {
     float2 y[4][4];                     // [j][p]: step 1 over v[j + 4 q]
 #pragma unroll
@@ -161,14 +178,12 @@ __device__ __forceinline__ void dft16(float2 *v) {
         for (int q = 0; q < 4; ++q) y[j][q] = v[j + 4 * q];
         dft<4>(y[j]);
     }
-    constexpr Tw4 w1 = tw4_of(1, 16), w2 = tw4_of(2, 16), w3 = tw4_of(3, 16);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        float2 z[4] = {y[0][p], y[1][p], y[2][p], y[3][p]};
-        if (p == 0)
-            dft<4>(z);
-        else
-            dft4_tw(z, p == 1 ? w1 : p == 2 ? w2 : w3);
+        float2 z[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z[j] = rot16(y[j][p], j * p);
+        dft<4>(z);
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[p + 4 * k] = z[k];
     }

@@ -358,8 +358,8 @@ __global__ __launch_bounds__(1024) void k_fft2d(const float2 *in, float2 *out,
 // register steps with three barriers: along y first, so that a thread's first
 // step takes its inputs straight from HBM (lanes on consecutive columns), then
 // along x, whose last step stores straight to HBM (lanes on RA consecutive
-// frequencies).  A line's step of length RB carries the twiddles exp(+2 pi i p j /
-// N) in its butterflies.  The centring of Eq. 1 needs no factors: rows and columns
+// frequencies).  A line's step of length RB starts with the twiddles exp(+2 pi i p j /
+// N).  The centring of Eq. 1 needs no factors: rows and columns
 // are read and written half a side further on.  A thread's RA inputs of the next
 // image are loaded once its own first step is done, so the whole next image is in
 // flight during the remaining steps.  Rows of one LDS image lie N + 1 apart.
@@ -375,24 +375,42 @@ template <> struct P2Cfg<64> { static constexpr int RA = 8, RB = 8; };
 template <> struct P2Cfg<32> { static constexpr int RA = 8, RB = 4; };
 template <> struct P2Cfg<16> { static constexpr int RA = 4, RB = 4; };
 
+// Nothing in these steps may pass FP32's range that the skies do not, since they
+// leave the chip as they are: every factor is a product before a sum (dft<8> forms
+// x +- y before it takes 1 / sqrt(2), dft8_tw |tan| y before the cosine).
 template <int R> __device__ __forceinline__ void p2_dft(float2 *v) {
-    if constexpr (R == 16)
+    if constexpr (R == 16) {
         dft16(v);
-    else
+    } else if constexpr (R == 8) {
+        float2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+        dft<4>(e);
+        dft<4>(o);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float2 r = rot16(o[p], 2 * p);
+            v[p] = cadd(e[p], r);
+            v[p + 4] = csub(e[p], r);
+        }
+    } else {
         dft<R>(v);
+    }
 }
-// Twiddles of the block of frequency p: w = exp(+2 pi i p / N).
-template <int N> __device__ __forceinline__ auto p2_tw(int p) {
-    if constexpr (N == 128) return kRoots.r8[p];
-    else if constexpr (N == 64) return kRoots.r8[2 * p];
-    else if constexpr (N == 32) return kRoots.r4[p];
-    else return kRoots.r4[2 * p];
+// Step of length R on the block of frequency p: twiddles w[q - 1] = exp(+2 pi i p q / N).
+template <int N, int R> __device__ __forceinline__ void p2_twiddles(float2 *w, const float2 *tw, int p) {
+#pragma unroll
+    for (int q = 1; q < R; ++q) w[q - 1] = tw[p * q];
+}
+template <int R> __device__ __forceinline__ void p2_dft_tw(float2 *x, const float2 *w) {
+#pragma unroll
+    for (int q = 1; q < R; ++q) x[q] = cmul(x[q], w[q - 1]);
+    p2_dft<R>(x);
 }
 
 template <int N>
 __global__ __launch_bounds__((N * P2Cfg<N>::RB)) void k_fft2d_p2(
     const float2 *in, float2 *out, const int32_t *__restrict__ chans, int n_chans,
-    const int64_t *__restrict__ grid_off, int P, int64_t grid_t_stride, int64_t n_img) {
+    const int64_t *__restrict__ grid_off, int P, int64_t grid_t_stride, int64_t n_img,
+    const float2 *__restrict__ tw) {
     constexpr int RA = P2Cfg<N>::RA, RB = P2Cfg<N>::RB, T = N * RB, NB = RA / RB;
     constexpr int pitch = N + 1, half = N / 2;
     extern __shared__ float2 sbuf[];
@@ -415,7 +433,9 @@ __global__ __launch_bounds__((N * P2Cfg<N>::RB)) void k_fft2d_p2(
     };
     // step 4: block p of row r (+ T / RA per further unit)
     const int p4 = tid % RA, r4 = tid / RA;
-    const auto tw4 = p2_tw<N>(p4);
+    // read per image: held, its fourteen registers spill
+    float2 *twl = sbuf + N * pitch;
+    for (int i = tid; i < N; i += T) twl[i] = tw[i];
     int64_t img = blockIdx.x;
     if (img < n_img) load(img);
     for (; img < n_img; img += gridDim.x) {
@@ -433,7 +453,9 @@ __global__ __launch_bounds__((N * P2Cfg<N>::RB)) void k_fft2d_p2(
             float2 x[RB];
 #pragma unroll
             for (int q = 0; q < RB; ++q) x[q] = s[q * pitch];
-            dft_tw(x, p2_tw<N>(p));
+            float2 w[RB - 1];
+            p2_twiddles<N, RB>(w, tw, p);
+            p2_dft_tw<RB>(x, w);
 #pragma unroll
             for (int q = 0; q < RB; ++q) s[q * pitch] = x[q];
         }
@@ -456,7 +478,9 @@ __global__ __launch_bounds__((N * P2Cfg<N>::RB)) void k_fft2d_p2(
             float2 x[RB];
 #pragma unroll
             for (int q = 0; q < RB; ++q) x[q] = s[q];
-            dft_tw(x, tw4);
+            float2 w[RB - 1];
+            p2_twiddles<N, RB>(w, twl, p4);
+            p2_dft_tw<RB>(x, w);
             const int ky = r / RB + RA * (r % RB);
             float2 *d = dst + (ky ^ half) * N;
 #pragma unroll
@@ -602,7 +626,7 @@ epic_status staged_image(epic_plan p, const void *d_grid, int n_time, void *d_sk
             const int64_t gts = p->grid_elems_per_t;
 #define EPIC_FFT2D(NN)                                                                         \
     hipLaunchKernelGGL(k_fft2d_p2<NN>, dim3(blocks), dim3(threads), lds2, s, src, dst, chans,  \
-                       n_chans, goff, p->P, gts, n_img)
+                       n_chans, goff, p->P, gts, n_img, twd)
             if (kp2) {
                 if (N == 128) EPIC_FFT2D(128);
                 else if (N == 64) EPIC_FFT2D(64);
