@@ -549,6 +549,8 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 constexpr int kPairRow = 65, kPairGrid = 64 * kPairRow;
+// elements whose staged voltages fit beside the two grids in a CU's 160 KiB: 1920
+constexpr int kPairMaxAnt = 160 * 1024 / 16 - 2 * kPairGrid;
 
 // The gather puts grid row or column m = j + 8 q at position 8 j + q: a 16-byte
 // read serves 16 lanes at once, eight rows (or columns) of two neighbouring j,
@@ -1824,11 +1826,14 @@ static epic_status queue_build(epic_plan p, hipStream_t s) {
 epic_status fused_build(epic_plan p, const std::vector<int> &j0, const std::vector<double> &w,
                         hipStream_t s) {
     const int A = p->A, K = p->K;
-    // Paired items: two feeds, N = 2 * 64, every element row in a 64-row window.
+    // Paired items: two feeds, N = 2 * 64, every element row in a 64-row window, and
+    // no more elements than the LDS beside two grids takes (one class per item, with
+    // one grid, takes about 6000).
     std::vector<int> pair_ylo(p->C, -1);
     const bool queue = (p->flags & EPIC_BATCH_QUEUE) != 0;
     for (int c = 0; c < p->C; ++c) {
-        if (queue) break;                 // the queue takes single-class items only
+        // the queue takes single-class items only
+        if (queue || A > kPairMaxAnt) break;
         if (p->banded[c] || p->P != 2 || p->ch[c].M != 64 || p->ch[c].R != 2) continue;
         int lo = 1 << 30, hi = -1;
         for (int a = 0; a < A; ++a) {
@@ -2028,7 +2033,7 @@ template <bool JN>
 static epic_status launch_pair(const FusedGroup *g, const uint8_t *d_volt, int64_t vstride, int A,
                                int vb, int n_time, float *acc, int32_t *autos, const FrameOut &fo,
                                hipStream_t s, bool dry, float *part) {
-    // the LDS left beside the two grids holds 1920 elements
+    static_assert(kPairMaxAnt <= 4 * 512, "four elements a thread cover every paired plan");
     if (A <= 512)
         return launch_pair_ar<1, JN>(g, d_volt, vstride, A, vb, n_time, acc, autos, fo, s, dry, part);
     if (A <= 1024)
