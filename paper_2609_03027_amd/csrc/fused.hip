@@ -24,6 +24,7 @@
 
 #include "internal.h"
 #include "lines.h"
+#include "slices.h"
 
 namespace epic {
 
@@ -748,7 +749,8 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
     const int slice = blockIdx.x / n_items;
     const FusedItem &it = items[blockIdx.x % n_items];
     if (it.c < 0) return;
-    const int t0 = slice * tps, t1 = min(n_time, t0 + tps);
+    // sample numbers that may pass n_time (up to 2^31 - 1 in frame mode) are unsigned
+    const int t0 = slice * tps, t1 = (int)min((uint32_t)n_time, (uint32_t)t0 + (uint32_t)tps);
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lo = tid & 7, j = (tid >> 3) & 7;
@@ -768,19 +770,19 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
     const bool own_autos = autos != nullptr && it.ox == 0;
     int sa[AR][4];
     uint32_t rx[AR], ry[AR];             // the next sample's voltages of elements tid + k T
-    auto fetch = [&](int t) {
+    auto fetch = [&](uint32_t t) {
         const uint8_t *vt = vbase + (int64_t)t * volt_t_stride;
 #pragma unroll
         for (int k = 0; k < AR; ++k) {
             const int a = tid + k * T;
-            if (a < A && t < t1) {
+            if (a < A && t < (uint32_t)t1) {
                 rx[k] = volt_raw(vt, a, vb);
                 ry[k] = volt_raw(vt, A + a, vb);
             }
         }
     };
-    auto put = [&](int t) {              // stage sample t, add its self terms
-        if (t >= t1) return;
+    auto put = [&](uint32_t t) {              // stage sample t, add its self terms
+        if (t >= (uint32_t)t1) return;
 #pragma unroll
         for (int k = 0; k < AR; ++k) {
             const int a = tid + k * T;
@@ -803,7 +805,7 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
 #pragma unroll
         for (int q = 0; q < 4; ++q) sa[k][q] = 0;
     }
-    fetch(t0);
+    fetch((uint32_t)t0);
     constexpr int HB = JN ? 1 : 5, JB = JN ? 3 : 1;
     PairTap held[2 * HB];
     JonesTap jt[JB];
@@ -816,8 +818,8 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
 #pragma unroll
         for (int k = 0; k < 2 * HB; ++k) held[k] = pair_tap(ent[(int64_t)min(k, n_iter - 1) * T]);
     }
-    put(t0);
-    fetch(t0 + 1);
+    put((uint32_t)t0);
+    fetch((uint32_t)t0 + 1u);
     __syncthreads();
 
     for (int t = t0 - 1; t < t1; ++t) {
@@ -850,8 +852,8 @@ __global__ __launch_bounds__(512) void k_fused_pair(const FusedItem *__restrict_
         __syncthreads();
         // phase 2
         if (t + 1 < t1) {
-            put(t + 2);
-            fetch(t + 3);
+            put((uint32_t)t + 2u);
+            fetch((uint32_t)t + 3u);
             pair_x(oth + (8 * w + lo) * kPairRow, j, tw[0]);
             __syncthreads();
         }
@@ -1130,7 +1132,8 @@ __attribute__((amdgpu_waves_per_eu(M == 16 ? 3 : 2))) void k_fused_rows(
     const int slice = blockIdx.x / n_items;
     const FusedItem &it = items[blockIdx.x % n_items];
     if (it.c < 0) return;
-    const int t0 = slice * tps, t1 = min(n_time, t0 + tps);
+    // sample numbers that may pass n_time (up to 2^31 - 1 in frame mode) are unsigned
+    const int t0 = slice * tps, t1 = (int)min((uint32_t)n_time, (uint32_t)t0 + (uint32_t)tps);
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
@@ -1161,19 +1164,19 @@ __attribute__((amdgpu_waves_per_eu(M == 16 ? 3 : 2))) void k_fused_rows(
     const bool own_autos = AR == 1 && autos != nullptr && it.ox == 0;
     int sa[4] = {0, 0, 0, 0};
     uint32_t rx[AR], ry[AR];             // the next sample's voltages of elements tid + k T
-    auto fetch = [&](int t) {
+    auto fetch = [&](uint32_t t) {
         const uint8_t *vt = vbase + (int64_t)t * volt_t_stride;
 #pragma unroll
         for (int k = 0; k < AR; ++k) {
             const int a = tid + k * T;
-            if (a < A && t < t1) {
+            if (a < A && t < (uint32_t)t1) {
                 rx[k] = volt_raw(vt, a, vb);
                 ry[k] = volt_raw(vt, A + a, vb);
             }
         }
     };
-    auto put = [&](int t) {              // stage sample t, add its self terms
-        if (t >= t1) return;
+    auto put = [&](uint32_t t) {              // stage sample t, add its self terms
+        if (t >= (uint32_t)t1) return;
 #pragma unroll
         for (int k = 0; k < AR; ++k) {
             const int a = tid + k * T;
@@ -1197,9 +1200,9 @@ __attribute__((amdgpu_waves_per_eu(M == 16 ? 3 : 2))) void k_fused_rows(
     };
 #pragma unroll
     for (int k = 0; k < AR; ++k) rx[k] = ry[k] = 0u;
-    fetch(t0);
-    put(t0);
-    fetch(t0 + 1);
+    fetch((uint32_t)t0);
+    put((uint32_t)t0);
+    fetch((uint32_t)t0 + 1u);
 
     const int col = w * C::CW + lane % C::CW, jy = lane / C::CW;
     for (int t = t0; t < t1; ++t) {
@@ -1208,8 +1211,8 @@ __attribute__((amdgpu_waves_per_eu(M == 16 ? 3 : 2))) void k_fused_rows(
         __syncthreads();                 // staged voltages, zeroed grid
         rows_gather<T>(smem, ent, n_iter, stage, e);
         __syncthreads();
-        put(t + 1);
-        fetch(t + 2);
+        put((uint32_t)t + 1u);
+        fetch((uint32_t)t + 2u);
         for (int g = (w + (int)blockIdx.x) % W; g < (C::H + 15) / 16; g += W)
             rows_x<M>(smem, 16 * g + (lane & 15), lane >> 4, twx);
         __syncthreads();
@@ -1635,33 +1638,6 @@ static int64_t fused_slots(epic_plan p, int M) {
            : M == 32 ? fused_slots_t<32, 2, false>(p->A) : fused_slots_t<16, 2, false>(p->A);
 }
 
-// Time slices of a call of a paired or row-unfolded group.  `slots` workgroups
-// run at once (one paired workgroup fills a CU), so the call takes
-// ceil(workgroups / slots) rounds of (samples per slice + a start and
-// an end that cost about six samples); more than one slice adds the partial
-// image sets' write and read (at about 4 TB/s against 4.5 us per sample) and
-// the reduction's launch.  The cheapest count wins: 1 where the items alone
-// fill whole rounds (128 channels on 256 CUs), 64 for one channel.  Frames
-// need no partial sets, only slices of whole frames.
-static int pair_slices(int64_t n_items, int64_t slots, int n_time, int s_max, int64_t part_floats,
-                       int unit) {
-    int best = 1;
-    double best_cost = 0.0;
-    for (int S = 1; S <= s_max; ++S) {
-        const int64_t tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
-        const int64_t used = (n_time + tps - 1) / tps;
-        if (used != S) continue;
-        const double rounds = std::ceil((double)(n_items * used) / (double)slots);
-        const double sets = unit > 1 || S == 1 ? 0.0 : 1.0 + (double)S * part_floats * 8.0 / 18e6;
-        const double cost = rounds * ((double)tps + 6.0) + sets;
-        if (S == 1 || cost < 0.97 * best_cost) {
-            best = S;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
-
 static int cu_count() {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -2005,7 +1981,7 @@ static epic_status launch_pair_fr(const FusedGroup *g, const uint8_t *d_volt, in
     const int unit = FR ? fo.len : 1;
     const int want = FR ? 64 : part && acc ? g->slices : 1;
     const int S = pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit);
-    const int tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
+    const int tps = slice_len(n_time, S, unit);
     float *sets = !FR && S > 1 ? part : nullptr;
     hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(512), lds, s, g->items.as<FusedItem>(),
                        g->entries.as<uint4>(), d_volt, vstride, A, n_time, acc, autos, fo.len,
@@ -2055,8 +2031,8 @@ static epic_status launch_rows_fr(const FusedGroup *g, const uint8_t *d_volt, in
     int S = fixed_slices && !FR
                 ? want
                 : pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit);
-    const int tps = ((n_time + S - 1) / S + unit - 1) / unit * unit;
-    S = (n_time + tps - 1) / tps;
+    const int tps = slice_len(n_time, S, unit);
+    S = (int)(((int64_t)n_time + tps - 1) / tps);
     float *sets = !FR && S > 1 ? part : nullptr;
     hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(C::T), C::lds(A), s,
                        g->items.as<FusedItem>(), g->entries.as<uint4>(), d_volt, vstride, A,
