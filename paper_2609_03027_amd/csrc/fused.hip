@@ -1697,7 +1697,7 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
         // most 64 and 256 MiB of partial image sets
         const int cap = (int)std::min<int64_t>(64, (int64_t{256} << 20) / (4 * std::max<int64_t>(1, n)));
         for (int nt = 4; nt <= 65536; nt *= 2)
-            g->slices = std::max(g->slices, pair_slices((int64_t)items.size(), g->slots, nt, std::max(1, cap), n, 1));
+            g->slices = std::max(g->slices, pair_slices((int64_t)items.size(), g->slots, nt, std::max(1, cap), n, 1, false));
     }
     epic_status st;
     if ((st = g->chans.alloc(sizeof(GroupChan) * std::max<size_t>(1, chans.size())))) return st;
@@ -1980,7 +1980,7 @@ static epic_status launch_pair_fr(const FusedGroup *g, const uint8_t *d_volt, in
     if (st || dry) return st;
     const int unit = FR ? fo.len : 1;
     const int want = FR ? 64 : part && acc ? g->slices : 1;
-    const int S = pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit);
+    const int S = pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit, FR);
     const int tps = slice_len(n_time, S, unit);
     float *sets = !FR && S > 1 ? part : nullptr;
     hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(512), lds, s, g->items.as<FusedItem>(),
@@ -2030,7 +2030,7 @@ static epic_status launch_rows_fr(const FusedGroup *g, const uint8_t *d_volt, in
     const int want = FR ? 64 : part && acc ? g->slices : 1;
     int S = fixed_slices && !FR
                 ? want
-                : pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit);
+                : pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit, FR);
     const int tps = slice_len(n_time, S, unit);
     S = (int)(((int64_t)n_time + tps - 1) / tps);
     float *sets = !FR && S > 1 ? part : nullptr;
