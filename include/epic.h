@@ -206,15 +206,18 @@ typedef struct {
                                     bytes per sample (EPIC_ERR_ARG): the [c][p][a] block of
                                     each sample is packed, samples may be spaced further
                                     apart (a ring with headers, a larger capture buffer) */
-    int32_t time_slices;         /* fused size groups of one class per item (paired groups
-                                    take the library's choice for 0 and none otherwise)
-                                    and the work queue (EPIC_F32): split
+    int32_t time_slices;         /* fused size groups and the work queue (EPIC_F32): split
                                     each call's samples into this many time slices, each
-                                    summed into its own partial image set and reduced in
-                                    slice order (deterministic for a given value; other
+                                    summed into its own partial image set and reduced in a
+                                    fixed order (deterministic for a given value; other
                                     values change the FP32 summation order only).  0 = the
                                     library's choice (enough workgroups for about four
-                                    waves per SIMD); 1 .. 64, else EPIC_ERR_ARG.  The
+                                    waves per SIMD; paired and row-unfolded groups choose per
+                                    call, within sets of at most 96 MiB); 1 .. 64, else
+                                    EPIC_ERR_ARG.  Paired groups (128 x 128, two feeds, rows
+                                    within 64) take no slices for any value but 0.  The sets
+                                    are part of the accumulator (epic_plan_info.bytes_acc,
+                                    epic_plan_footprint): 1 leaves them out.  The
                                     autotuner's third knob */
 } epic_plan_desc;
 

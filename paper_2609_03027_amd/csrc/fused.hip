@@ -1692,13 +1692,8 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
     }
     g->part_floats = n;
     g->n_chans = (int)chans.size();
-    if (g->kind != 0 && p->time_slices == 0) {
-        // room for the most slices that a call would take (pair_slices), at
-        // most 64 and 256 MiB of partial image sets
-        const int cap = (int)std::min<int64_t>(64, (int64_t{256} << 20) / (4 * std::max<int64_t>(1, n)));
-        for (int nt = 4; nt <= 65536; nt *= 2)
-            g->slices = std::max(g->slices, pair_slices((int64_t)items.size(), g->slots, nt, std::max(1, cap), n, 1, false));
-    }
+    if (g->kind != 0 && p->time_slices == 0)
+        g->slices = reserved_slices((int64_t)items.size(), g->slots, n);
     epic_status st;
     if ((st = g->chans.alloc(sizeof(GroupChan) * std::max<size_t>(1, chans.size())))) return st;
     if (!chans.empty())
@@ -1980,8 +1975,8 @@ static epic_status launch_pair_fr(const FusedGroup *g, const uint8_t *d_volt, in
     if (st || dry) return st;
     const int unit = FR ? fo.len : 1;
     const int want = FR ? 64 : part && acc ? g->slices : 1;
-    const int S = pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit, FR);
-    const int tps = slice_len(n_time, S, unit);
+    const SliceChoice sl = best_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit, FR);
+    const int S = sl.slices, tps = sl.len;
     float *sets = !FR && S > 1 ? part : nullptr;
     hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(512), lds, s, g->items.as<FusedItem>(),
                        g->entries.as<uint4>(), d_volt, vstride, A, n_time, acc, autos, fo.len,
@@ -2028,11 +2023,9 @@ static epic_status launch_rows_fr(const FusedGroup *g, const uint8_t *d_volt, in
     if (st || dry) return st;
     const int unit = FR ? fo.len : 1;
     const int want = FR ? 64 : part && acc ? g->slices : 1;
-    int S = fixed_slices && !FR
-                ? want
-                : pair_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit, FR);
-    const int tps = slice_len(n_time, S, unit);
-    S = (int)(((int64_t)n_time + tps - 1) / tps);
+    const SliceChoice sl = best_slices(g->n_items, g->slots, n_time, want, g->part_floats, unit, FR);
+    const int tps = fixed_slices && !FR ? slice_len(n_time, want, unit) : sl.len;
+    const int S = (int)(((int64_t)n_time + tps - 1) / tps);
     float *sets = !FR && S > 1 ? part : nullptr;
     hipLaunchKernelGGL(kern, dim3(g->n_items * S), dim3(C::T), C::lds(A), s,
                        g->items.as<FusedItem>(), g->entries.as<uint4>(), d_volt, vstride, A,

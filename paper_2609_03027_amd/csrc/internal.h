@@ -111,7 +111,7 @@ struct FusedGroup {
     // are split over `slices` workgroups, each storing its Eq. 2 sums to its
     // own partial image set (part_floats floats, in the accumulator's working
     // memory at byte offset work_off); k_fused_reduce adds them in order.
-    // Paired groups: the most slices a call may take (pair_slices chooses).
+    // Kinds 1 and 2: the most slices a call may take (best_slices chooses).
     int slices = 1;
     int64_t part_floats = 0;
     int64_t work_off = 0;
