@@ -1607,8 +1607,19 @@ static void xcd_layout(std::vector<FusedItem> &items, int C) {
     items.swap(laid);
 }
 
-// Workgroups of a one-class-per-item group's kernel that the device runs at
-// once (occupancy API over all CUs), or 0 if unknown.
+// Workgroups of a kernel that the device runs at once (occupancy API over all
+// CUs), or 0 if unknown.
+static int64_t resident_slots(const void *k, int threads, size_t lds) {
+    if (lds_ready(k, lds)) return 0;
+    int dev = 0, n_cu = 0, per_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, lds) != hipSuccess)
+        return 0;
+    return (int64_t)n_cu * per_cu;
+}
+
+// The same for a one-class-per-item group.
 template <int M, int P, bool JN>
 static int64_t fused_slots_t(int A) {
     constexpr int T = FCfg<M>::T, GSZ = M * FCfg<M>::ROW;
@@ -1616,13 +1627,7 @@ static int64_t fused_slots_t(int A) {
     const void *k = A <= T       ? reinterpret_cast<const void *>(k_fused<M, P, 1, false, JN>)
                     : A <= 2 * T ? reinterpret_cast<const void *>(k_fused<M, P, 2, false, JN>)
                                  : reinterpret_cast<const void *>(k_fused<M, P, 4, false, JN>);
-    if (lds_ready(k, lds)) return 0;
-    int dev = 0, n_cu = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, T, lds) != hipSuccess)
-        return 0;
-    return (int64_t)n_cu * per_cu;
+    return resident_slots(k, T, lds);
 }
 
 static int64_t fused_slots(epic_plan p, int M) {
@@ -1636,6 +1641,16 @@ static int64_t fused_slots(epic_plan p, int M) {
                : M == 32 ? fused_slots_t<32, 2, true>(p->A) : fused_slots_t<16, 2, true>(p->A);
     return M == 64 ? fused_slots_t<64, 2, false>(p->A)
            : M == 32 ? fused_slots_t<32, 2, false>(p->A) : fused_slots_t<16, 2, false>(p->A);
+}
+
+// The same for a row-unfolded group, by the element rounds that its launch takes.
+template <int M>
+static int64_t rows_slots(int A) {
+    using C = RowsCfg<M>;
+    const void *k = A <= C::T       ? reinterpret_cast<const void *>(k_fused_rows<M, 1, false>)
+                    : A <= 2 * C::T ? reinterpret_cast<const void *>(k_fused_rows<M, 2, false>)
+                                    : reinterpret_cast<const void *>(k_fused_rows<M, 4, false>);
+    return resident_slots(k, C::T, C::lds(A));
 }
 
 static int cu_count() {
@@ -1675,8 +1690,11 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
     }
     if (p->time_slices > 0) S = p->time_slices;   // the caller's (autotuned) choice
     g->slices = g->kind == 0 || (g->kind == 2 && p->time_slices > 0) ? S : 1;
+    // a paired workgroup fills a CU; of row-unfolded ones as many as registers and the
+    // staged elements leave (M = 32: four a CU to about 950 elements, two with 2048)
     g->slots = cu_count();
-    if (g->kind == 2) g->slots *= g->M == 16 ? 12 : 4;   // resident workgroups
+    if (g->kind == 2)
+        if (const int64_t n = g->M == 32 ? rows_slots<32>(p->A) : rows_slots<16>(p->A)) g->slots = n;
     std::vector<int64_t> off(p->C, -1);
     std::vector<GroupChan> chans;
     int64_t n = 0;
