@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void k_auto_h(const double2 *__restrict__ R,
     // entry (product q, sign of d)
     constexpr int NH = P == 2 ? 3 : 1;
     const int q = threadIdx.x >> 1, neg = threadIdx.x & 1;
-    if (q >= NH) return;
+    if (q >= NH || (neg && 2 * d + 1 == D2)) return;   // the centre: one writer
     double2 o;
     if (q < 2)
         o = make_double2(tot[2 * q], neg ? -tot[2 * q + 1] : tot[2 * q + 1]);
