@@ -393,7 +393,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     pr[2] = (uint32_t)dot2(x, y, 0x7fffffff);
                     // xi yr - xr yi = xi yr + xr (~yi + 1)
                     pr[3] = (uint32_t)dot2(swap16(x), y ^ 0xffff0000u,
-                                           ((int)(x << 16) >> 16) + 0x7fffffff);
+                                           (int)((uint32_t)((int)(x << 16) >> 16) + 0x7fffffffu));
                 }
 #pragma unroll
                 for (int q = 0; q < NPROD; ++q)
