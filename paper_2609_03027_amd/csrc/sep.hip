@@ -460,6 +460,9 @@ __global__ __launch_bounds__((SepShape<DT, N>::T)) void k_sep(const SepArgs a) {
         // the two waves of a SIMD are not at the same phase.  Step 2 also
         // runs on the two intervals before the first sample, on zeros: a branch
         // around it would copy the sums.
+        // The two arms hold their barriers at different places of the source: a wave
+        // takes one arm whole (`wave` is uniform), both pass t_stop - t_begin + 2
+        // barriers, and the hardware's counts arriving waves, not places.
         auto run = [&](auto ahead) __attribute__((always_inline)) {
             for (int i = t_begin; i < t_stop + (ahead ? 1 : 2); ++i) {
                 const int b = (i - t_begin) & 1;
