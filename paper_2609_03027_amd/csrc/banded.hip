@@ -68,6 +68,16 @@ __device__ __forceinline__ uint32_t pk_load(const uint8_t *p, uint32_t idx) {
     if constexpr (P * VB == 2) return *reinterpret_cast<const uint16_t *>(p + 2u * idx);
     return p[idx];
 }
+// The same from the input layout (x feed: sample a, y feed: A + a of one (sample,
+// channel) block), as one word.
+template <int P, int VB>
+__device__ __forceinline__ uint32_t in_load(const uint8_t *p, uint32_t a, uint32_t A) {
+    auto one = [&](uint32_t i) -> uint32_t {
+        if constexpr (VB == 2) return *reinterpret_cast<const uint16_t *>(p + 2u * i);
+        return p[i];
+    };
+    return P == 2 ? one(a) | one(A + a) << (8 * VB) : one(a);
+}
 template <int VB>
 __device__ __forceinline__ int2 pk_x(uint32_t raw) {
     return volt_dec(raw & (VB == 2 ? 0xffffu : 0xffu), VB);
@@ -886,10 +896,9 @@ __device__ __forceinline__ void mf_tap(const uint4 e, const mf_h4 hv, uint32_t *
 
 template <int P, int VB>
 __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
-    const uint8_t *__restrict__ packed, int64_t pack_t, int64_t pack_row,
-    const BandChan *__restrict__ chans,
+    const uint8_t *__restrict__ volt, int64_t vstride, const BandChan *__restrict__ chans,
     const BandItem *__restrict__ items, int n_items, int G, int nt, int64_t per_xcd,
-    const uint4 *__restrict__ entries, const int32_t *__restrict__ ants,
+    const uint4 *__restrict__ entries, const int32_t *__restrict__ ants, int A,
     uint2 *__restrict__ scratch, int64_t scratch_t, const MfConst *__restrict__ mfc) {
     constexpr int N = 256, T = 128;
     // the two planes of BL * N FP16 cells (+ the spare slot), then the
@@ -914,7 +923,7 @@ __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
     const MfConst k = mf_consts(mfc, lane);
     const int32_t *al = ants + it.ant_off;
     const uint4 *ent = entries + it.entry_off;
-    const uint8_t *vc = packed + (int64_t)it.chan * pack_row;
+    const uint8_t *vc = volt + (int64_t)ch.c * P * A * VB;
     // the voltages of the elements that meet this band are decoded once per
     // sample into LDS as FP16 (exact for 4- and 8-bit integers; the entries
     // index this list); a lane's first two elements are read one sample
@@ -924,10 +933,10 @@ __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
     for (int j = 0; j < 2; ++j)
         if (tid + j * T < it.n_ants) ai[j] = (uint32_t)al[tid + j * T];
     auto fetch = [&](int t) {
-        const uint8_t *vx = vc + (int64_t)t * pack_t;
+        const uint8_t *vx = vc + (int64_t)t * vstride;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            if (tid + j * T < it.n_ants) rx[j] = pk_load<P, VB>(vx, ai[j]);
+            if (tid + j * T < it.n_ants) rx[j] = in_load<P, VB>(vx, ai[j], (uint32_t)A);
     };
     if (t0 < t1) fetch(t0);
     // a lane list of at most MF_UN entries is read once for all the samples;
@@ -950,9 +959,9 @@ __global__ __launch_bounds__(128, 3) void k_band_rows_mf(
                 vst[tid + j * T] = mf_h4{(_Float16)x.x, (_Float16)x.y, (_Float16)y.x, (_Float16)y.y};
             }
         if (it.n_ants > 2 * T) {
-            const uint8_t *vx = vc + (int64_t)t * pack_t;
+            const uint8_t *vx = vc + (int64_t)t * vstride;
             for (int i = tid + 2 * T; i < it.n_ants; i += T) {
-                const uint32_t raw = pk_load<P, VB>(vx, (uint32_t)al[i]);
+                const uint32_t raw = in_load<P, VB>(vx, (uint32_t)al[i], (uint32_t)A);
                 const int2 x = pk_x<VB>(raw);
                 const int2 y = P == 2 ? pk_y<VB>(raw) : make_int2(0, 0);
                 vst[i] = mf_h4{(_Float16)x.x, (_Float16)x.y, (_Float16)y.x, (_Float16)y.y};
@@ -1136,7 +1145,7 @@ static epic_status band_items(epic_plan p, const std::vector<int> &j0,
                 const double sg = ((row + col) & 1) ? -1.0 : 1.0;
                 GatherTap tp{};
                 tp.cell = (row - r0) * N + col;
-                tp.ant = rank[a];
+                tp.ant = compact ? a : rank[a];
                 tp.wr = (float)(sg * w[wi]);
                 tp.wi = (float)(-sg * w[wi + 1]);
                 per[band].push_back(tp);
@@ -1370,7 +1379,7 @@ epic_status banded_build(epic_plan p, const std::vector<int> &j0, const std::vec
     bp.pack_row = ((int64_t)p->A * p->vb * p->P + 15) / 16 * 16;
     bp.pack_off = (bp.scratch_bytes + bp.part_bytes + 255) / 256 * 256;
     for (const BandSize &bs : bp.sizes)
-        if (bs.R) bp.pack_bytes = 2 * (int64_t)bp.t_chunk * bp.n * bp.pack_row;
+        if (bs.R && !mf) bp.pack_bytes = 2 * (int64_t)bp.t_chunk * bp.n * bp.pack_row;
     if ((st = bp.d_rank.alloc(sizeof(int32_t) * rank.size()))) return st;
     EPIC_HIP(hipMemcpyAsync(bp.d_rank.p, rank.data(), sizeof(int32_t) * rank.size(),
                             hipMemcpyHostToDevice, s));
@@ -1493,7 +1502,7 @@ static epic_status ready_mf(int P) {
 // FP16 four-step MFMA passes (256 x 256 channels of EPIC_F16_MFMA plans):
 // same grids and items as launch_pw<16, 2, P>; the scratch holds FP16 cells.
 template <int P>
-static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const uint8_t *packed,
+static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const uint8_t *d_volt,
                              int nt, float4 *scratch, float *part, float *acc, hipStream_t s) {
     const BandPlan &bp = p->band;
     const BandChan *chans = bp.d_chans.as<BandChan>() + bs.chan_off;
@@ -1510,13 +1519,13 @@ static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const ui
             return fail(EPIC_ERR_UNSUPPORTED, "FP16 four-step: more than 4096 elements in a band");
         if (p->vb == 2)
             hipLaunchKernelGGL((k_band_rows_mf<P, 2>), dim3((unsigned)(8 * per_xcd)), dim3(128),
-                               lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
-                               (int)bs.n_items, bs.G, nt, per_xcd, ent, ants, sc, bp.scratch_t,
+                               lds, s, d_volt, p->vstride(), chans, items, (int)bs.n_items, bs.G,
+                               nt, per_xcd, ent, ants, p->A, sc, bp.scratch_t,
                                bp.d_mf.as<MfConst>());
         else
             hipLaunchKernelGGL((k_band_rows_mf<P, 1>), dim3((unsigned)(8 * per_xcd)), dim3(128),
-                               lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
-                               (int)bs.n_items, bs.G, nt, per_xcd, ent, ants, sc, bp.scratch_t,
+                               lds, s, d_volt, p->vstride(), chans, items, (int)bs.n_items, bs.G,
+                               nt, per_xcd, ent, ants, p->A, sc, bp.scratch_t,
                                bp.d_mf.as<MfConst>());
         EPIC_HIP(hipGetLastError());
         return EPIC_OK;
@@ -1538,11 +1547,12 @@ static epic_status launch_mf(epic_plan p, const BandSize &bs, int pass, const ui
 
 template <int P>
 static epic_status launch_pw_any(epic_plan p, const BandSize &bs, int pass,
-                                 const uint8_t *packed, int nt, float4 *scratch, float *part,
-                                 float *acc, const FrameOut &fo, hipStream_t s) {
-    packed += bs.chan_off * p->band.pack_row;
+                                 const uint8_t *d_volt, const uint8_t *packed, int nt,
+                                 float4 *scratch, float *part, float *acc, const FrameOut &fo,
+                                 hipStream_t s) {
     if (p->precision == EPIC_F16_MFMA)
-        return launch_mf<P>(p, bs, pass, packed, nt, scratch, part, acc, s);
+        return launch_mf<P>(p, bs, pass, d_volt, nt, scratch, part, acc, s);
+    packed += bs.chan_off * p->band.pack_row;
     if (bs.R == 16) return launch_pw<16, 2, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
     if (bs.R == 8 && bs.NP == 2)
         return launch_pw<8, 2, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
@@ -1714,8 +1724,8 @@ epic_status banded_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, 
             for (const BandSize &bs : bp.sizes) {
                 if (bs.R)
                     st = p->P == 2
-                             ? launch_pw_any<2>(p, bs, pass, packed, nt, scratch, part, a, fr, qs)
-                             : launch_pw_any<1>(p, bs, pass, packed, nt, scratch, part, a, fr, qs);
+                             ? launch_pw_any<2>(p, bs, pass, v, packed, nt, scratch, part, a, fr, qs)
+                             : launch_pw_any<1>(p, bs, pass, v, packed, nt, scratch, part, a, fr, qs);
                 else
                     st = launch_generic(p, bs, pass, chans, v, nt, scratch, a, qs);
                 if (st) break;
