@@ -2221,8 +2221,12 @@ epic_status autos_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, i
         1, std::min<int64_t>(want / groups, ((int64_t)n_time + 64 * groups - 1) / (64 * groups)));
     const int t_chunk = (int)((n_time + chunks - 1) / chunks);
     dim3 grid((p->A + 255) / 256, p->C, (n_time + t_chunk - 1) / t_chunk);
+    // at least 256 threads, also where some have no samples: they share the clearing
+    // and the writing of the sums (5000 elements of one channel, 4 samples: 8.4 us on
+    // one wave each, 4.0 us so)
+    const int rows = std::max(groups, 256 / lanes);
 #define EPIC_AUTOS(PP, VV, EE)                                                               \
-    hipLaunchKernelGGL((k_autos<PP, VV, EE>), grid, dim3(lanes, groups), 0, s, d_volt,       \
+    hipLaunchKernelGGL((k_autos<PP, VV, EE>), grid, dim3(lanes, rows), 0, s, d_volt,         \
                        vstride, p->A, n_time, t_chunk, acc->d_autos.as<int32_t>())
     if (p->P == 2) {
         if (p->vb == 2) EPIC_AUTOS(2, 2, 1);
