@@ -338,8 +338,17 @@ __global__ __launch_bounds__(BT) void k_band_cols(const BandChan *__restrict__ c
 // not fit by scattered stores.  Bound by memory: 4096 elements x 2 feeds x 64
 // channels x 128 samples take 29 us, 134 MB read and written.  (Adding the self-term
 // sums here as well costs more than their own pass, which has fewer atomics.)
-constexpr int PKT = 256;
+constexpr int PKT = 1024;
 constexpr int64_t PK_LDS = 64 << 10;
+// Rounds are packed from these counts on; others read the input, the element of a
+// place by a table.  A pass costs its launch, 1 - 2 us (5000 elements, one 512^2
+// channel, 4 samples: 42.1 us without, 43.3 with), and saves what the scattered bytes
+// cost a band's taps: from about 2^18 elements x samples x channels (4096 x 64: 67.3
+// without, 66.9 with; 4096 x 256: 131.0 and 126.8; 20000 x 200: 350 and 309).  With a
+// few hundred elements a channel's voltages are a few lines anyway (100 x 64 channels
+// x 64 samples: 1208 and 1237 us; 300 elements 1237 and 1251).
+constexpr int PACK_ELEMENTS = 1000;
+constexpr int64_t PACK_ROUND = 1 << 18;
 
 template <int P, int VB>
 __global__ __launch_bounds__(PKT) void k_band_pack(const uint8_t *__restrict__ volt,
@@ -501,11 +510,13 @@ constexpr int cols_pitch() {
 
 // One batch of UN gather entries of a row-pass lane (iterations past n_iter
 // re-read the last one and become no-op padding entries aimed at LDS slot
-// spare) and the packed voltages they name.
-template <int UN, int P, int VB>
+// spare) and the voltages they name: packed, or (RAW) from the input layout, the
+// element of a place from by_rank.
+template <int UN, int P, int VB, bool RAW>
 __device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN],
                                         const uint4 *__restrict__ ent, int i0, int n_iter, int T,
-                                        int tid, const uint8_t *vx, int spare) {
+                                        int tid, const uint8_t *vx, int spare,
+                                        const int32_t *__restrict__ by_rank, int A) {
 #pragma unroll
     for (int k = 0; k < UN; ++k)
         e[k] = ent[(uint32_t)(min(i0 + k, n_iter - 1) * T + tid)];
@@ -514,7 +525,11 @@ __device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN],
         if (i0 + k >= n_iter) e[k] = make_uint4(0u, (uint32_t)spare, 0u, 0u);
 #pragma unroll
     for (int k = 0; k < UN; ++k) {
-        bx[k] = pk_load<P, VB>(vx, e[k].x & 0x7fffffffu);
+        const uint32_t place = e[k].x & 0x7fffffffu;
+        if constexpr (RAW)
+            bx[k] = in_load<P, VB>(vx, (uint32_t)by_rank[place], (uint32_t)A);
+        else
+            bx[k] = pk_load<P, VB>(vx, place);
     }
 }
 
@@ -524,10 +539,10 @@ __device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN],
 // the extra registers cost more occupancy than the reuse gained.)
 // Bound by the scratch writes: 6.75 GB (64 channels of 256^2, 128 samples) take
 // 1.25 - 1.45 ms; with the voltages read as scattered bytes they took 1.55 - 1.75.
-template <int R, int NP, int P, int VB>
+template <int R, int NP, int P, int VB, bool RAW>
 __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
-    const uint8_t *__restrict__ packed, int64_t pack_t, int64_t pack_row,
-    const BandChan *__restrict__ chans,
+    const uint8_t *__restrict__ volt, int64_t volt_t, int64_t pack_row,
+    const int32_t *__restrict__ by_rank, int A, const BandChan *__restrict__ chans,
     const BandItem *__restrict__ items, int n_items, int G, int nt, int64_t per_xcd,
     const uint4 *__restrict__ entries, float4 *__restrict__ scratch, int64_t scratch_t) {
     constexpr int N = Pw<R, NP>::N, L = Pw<R, NP>::L, T = rows_threads<R, NP>();
@@ -554,19 +569,20 @@ __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
     // entries and voltages is loaded before the barrier that publishes the
     // zeroed band, so its two dependent loads overlap the fill and the
     // barrier.
-    const uint8_t *vx = packed + (int64_t)t * pack_t + (int64_t)it.chan * pack_row;
+    const uint8_t *vx = volt + (int64_t)t * volt_t +
+                        (RAW ? (int64_t)ch.c * P * A * VB : (int64_t)it.chan * pack_row);
     const uint4 *ent = entries + it.entry_off;
     const int n_iter = it.n_iter;
     uint4 e[UN];
     uint32_t bx[UN];
-    if (n_iter > 0) pw_load<UN, P, VB>(e, bx, ent, 0, n_iter, T, tid, vx, BLR * N);
+    if (n_iter > 0) pw_load<UN, P, VB, RAW>(e, bx, ent, 0, n_iter, T, tid, vx, BLR * N, by_rank, A);
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int k = 0; k < BLR * N / T; ++k) lds[tid + k * T] = zero;
     __syncthreads();
     float4 s = zero;
     for (int i0 = 0; i0 < n_iter; i0 += UN) {
-        if (i0) pw_load<UN, P, VB>(e, bx, ent, i0, n_iter, T, tid, vx, BLR * N);
+        if (i0) pw_load<UN, P, VB, RAW>(e, bx, ent, i0, n_iter, T, tid, vx, BLR * N, by_rank, A);
 #pragma unroll
         for (int k = 0; k < UN; ++k) {
             if (k % 4 == 0 && i0 + k >= n_iter) break;   // uniform; up to three padding taps
@@ -1379,9 +1395,12 @@ epic_status banded_build(epic_plan p, const std::vector<int> &j0, const std::vec
     bp.pack_row = ((int64_t)p->A * p->vb * p->P + 15) / 16 * 16;
     bp.pack_off = (bp.scratch_bytes + bp.part_bytes + 255) / 256 * 256;
     for (const BandSize &bs : bp.sizes)
-        if (bs.R && !mf) bp.pack_bytes = 2 * (int64_t)bp.t_chunk * bp.n * bp.pack_row;
+        if (bs.R && !mf && p->A >= PACK_ELEMENTS) bp.pack_bytes = 2 * (int64_t)bp.t_chunk * bp.n * bp.pack_row;
     if ((st = bp.d_rank.alloc(sizeof(int32_t) * rank.size()))) return st;
+    if ((st = bp.d_by_rank.alloc(sizeof(int32_t) * by_rank.size()))) return st;
     EPIC_HIP(hipMemcpyAsync(bp.d_rank.p, rank.data(), sizeof(int32_t) * rank.size(),
+                            hipMemcpyHostToDevice, s));
+    EPIC_HIP(hipMemcpyAsync(bp.d_by_rank.p, by_rank.data(), sizeof(int32_t) * by_rank.size(),
                             hipMemcpyHostToDevice, s));
     if ((st = bp.d_chans.alloc(sizeof(BandChan) * bp.host.size()))) return st;
     EPIC_HIP(hipMemcpyAsync(bp.d_chans.p, bp.host.data(), sizeof(BandChan) * bp.host.size(),
@@ -1408,12 +1427,13 @@ epic_status banded_build(epic_plan p, const std::vector<int> &j0, const std::vec
 }
 
 template <int R, int NP>
-static const void *rows_pw_kernel(int P, int vb) {
-    if (vb == 2)
-        return P == 2 ? reinterpret_cast<const void *>(k_band_rows_pw<R, NP, 2, 2>)
-                      : reinterpret_cast<const void *>(k_band_rows_pw<R, NP, 1, 2>);
-    return P == 2 ? reinterpret_cast<const void *>(k_band_rows_pw<R, NP, 2, 1>)
-                  : reinterpret_cast<const void *>(k_band_rows_pw<R, NP, 1, 1>);
+static auto rows_pw_kernel(int P, int vb, bool raw) {
+    if (raw) {
+        if (vb == 2) return P == 2 ? k_band_rows_pw<R, NP, 2, 2, true> : k_band_rows_pw<R, NP, 1, 2, true>;
+        return P == 2 ? k_band_rows_pw<R, NP, 2, 1, true> : k_band_rows_pw<R, NP, 1, 1, true>;
+    }
+    if (vb == 2) return P == 2 ? k_band_rows_pw<R, NP, 2, 2, false> : k_band_rows_pw<R, NP, 1, 2, false>;
+    return P == 2 ? k_band_rows_pw<R, NP, 2, 1, false> : k_band_rows_pw<R, NP, 1, 1, false>;
 }
 template <int R, int NP>
 static const void *cols_pw_kernel(int P) {
@@ -1430,16 +1450,18 @@ static size_t cols_pw_lds() {
 }
 
 template <int R, int NP>
-static epic_status ready_pw(int P) {
-    epic_status st = lds_ready(rows_pw_kernel<R, NP>(P, 1), rows_pw_lds<R, NP>());
-    if (!st) st = lds_ready(rows_pw_kernel<R, NP>(P, 2), rows_pw_lds<R, NP>());
+static epic_status ready_pw(int P, int vb) {
+    epic_status st = EPIC_OK;
+    for (int raw = 0; raw < 2 && !st; ++raw)
+        st = lds_ready(reinterpret_cast<const void *>(rows_pw_kernel<R, NP>(P, vb, raw)),
+                       rows_pw_lds<R, NP>());
     if (!st) st = lds_ready(cols_pw_kernel<R, NP>(P), cols_pw_lds<R, NP>());
     return st;
 }
 
 template <int R, int NP, int P>
-static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const uint8_t *packed,
-                             int nt, float4 *scratch, float *part, float *acc,
+static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const uint8_t *d_volt,
+                             const uint8_t *packed, int nt, float4 *scratch, float *part, float *acc,
                              const FrameOut &fo, hipStream_t s) {
     const BandPlan &bp = p->band;
     const BandChan *chans = bp.d_chans.as<BandChan>() + bs.chan_off;
@@ -1451,14 +1473,11 @@ static epic_status launch_pw(epic_plan p, const BandSize &bs, int pass, const ui
         const size_t lds = rows_pw_lds<R, NP>();
         const BandItem *items = bp.d_items.as<BandItem>() + bs.item_off;
         const uint4 *ent = bp.d_entries.as<uint4>();
-        if (p->vb == 2)
-            hipLaunchKernelGGL((k_band_rows_pw<R, NP, P, 2>), dim3((unsigned)(8 * per_xcd)),
-                               dim3(T), lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
-                               (int)bs.n_items, bs.G, nt, per_xcd, ent, scratch, bp.scratch_t);
-        else
-            hipLaunchKernelGGL((k_band_rows_pw<R, NP, P, 1>), dim3((unsigned)(8 * per_xcd)),
-                               dim3(T), lds, s, packed, bp.n * bp.pack_row, bp.pack_row, chans, items,
-                               (int)bs.n_items, bs.G, nt, per_xcd, ent, scratch, bp.scratch_t);
+        hipLaunchKernelGGL((rows_pw_kernel<R, NP>(P, p->vb, !packed)), dim3((unsigned)(8 * per_xcd)),
+                           dim3(T), lds, s, packed ? packed : d_volt,
+                           packed ? bp.n * bp.pack_row : p->vstride(), bp.pack_row,
+                           bp.d_by_rank.as<int32_t>(), p->A, chans, items, (int)bs.n_items, bs.G, nt,
+                           per_xcd, ent, scratch, bp.scratch_t);
         EPIC_HIP(hipGetLastError());
         return EPIC_OK;
     }
@@ -1552,11 +1571,11 @@ static epic_status launch_pw_any(epic_plan p, const BandSize &bs, int pass,
                                  hipStream_t s) {
     if (p->precision == EPIC_F16_MFMA)
         return launch_mf<P>(p, bs, pass, d_volt, nt, scratch, part, acc, s);
-    packed += bs.chan_off * p->band.pack_row;
-    if (bs.R == 16) return launch_pw<16, 2, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
+    if (packed) packed += bs.chan_off * p->band.pack_row;
+    if (bs.R == 16) return launch_pw<16, 2, P>(p, bs, pass, d_volt, packed, nt, scratch, part, acc, fo, s);
     if (bs.R == 8 && bs.NP == 2)
-        return launch_pw<8, 2, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
-    return launch_pw<8, 3, P>(p, bs, pass, packed, nt, scratch, part, acc, fo, s);
+        return launch_pw<8, 2, P>(p, bs, pass, d_volt, packed, nt, scratch, part, acc, fo, s);
+    return launch_pw<8, 3, P>(p, bs, pass, d_volt, packed, nt, scratch, part, acc, fo, s);
 }
 
 static const void *pack_kernel(int P, int vb) {
@@ -1662,11 +1681,11 @@ epic_status banded_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, 
         if (p->precision == EPIC_F16_MFMA) {
             st = ready_mf(p->P);
         } else if (bs.R == 16) {
-            st = ready_pw<16, 2>(p->P);
+            st = ready_pw<16, 2>(p->P, p->vb);
         } else if (bs.R == 8 && bs.NP == 2) {
-            st = ready_pw<8, 2>(p->P);
+            st = ready_pw<8, 2>(p->P, p->vb);
         } else if (bs.R == 8) {
-            st = ready_pw<8, 3>(p->P);
+            st = ready_pw<8, 3>(p->P, p->vb);
         } else {
             const size_t lds1 = sizeof(float4) * 2 * BL * bs.N;
             const size_t lds2 = sizeof(float4) * 2 * BL * (bs.N + 1);
@@ -1716,8 +1735,11 @@ epic_status banded_accumulate(epic_plan p, epic_acc acc, const uint8_t *d_volt, 
         if (split && k >= 2) EPIC_HIP(hipStreamWaitEvent(q_rows, ev[3 + b], 0));
         // (the packed half is free as well: its row pass ended before the column
         // pass that the event stands for)
-        uint8_t *packed = acc->d_work.as<uint8_t>() + bp.pack_off + b * (bp.pack_bytes / 2);
-        if (bp.pack_bytes) st = launch_pack(p, v, nt, packed, q_rows);
+        uint8_t *packed = nullptr;
+        if (bp.pack_bytes && (int64_t)p->A * bp.n * nt >= PACK_ROUND) {
+            packed = acc->d_work.as<uint8_t>() + bp.pack_off + b * (bp.pack_bytes / 2);
+            st = launch_pack(p, v, nt, packed, q_rows);
+        }
         for (int pass = 0; pass < 2 && !st; ++pass) {
             const hipStream_t qs = pass ? q_cols : q_rows;
             if (split && pass == 1) EPIC_HIP(hipStreamWaitEvent(q_cols, ev[1 + b], 0));

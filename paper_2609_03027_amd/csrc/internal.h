@@ -188,6 +188,7 @@ struct BandPlan {
     // in the order d_rank gives (by place, so that a band's lie together)
     int64_t pack_off = 0, pack_row = 0, pack_bytes = 0;
     DevBuf d_rank;           // int32 [A]: place of element a in the packed order
+    DevBuf d_by_rank;        // int32 [A]: the element at a place
     std::vector<BandSize> sizes;
     std::vector<BandChan> host;
     DevBuf d_chans;          // BandChan[n]
