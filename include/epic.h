@@ -144,9 +144,10 @@ typedef enum {
                                   persistent launch -- workgroups take units from a device
                                   work queue, largest transforms first (64 x 64 classes, then
                                   bundles of four 32 x 32 or eight 16 x 16 classes of one
-                                  channel).  Classes are not paired and samples are not split
-                                  into time slices (each class owns its pixels, so results are
-                                  deterministic).  FP32, one kernel per element; not with
+                                  channel), one per time slice of the size's group (see
+                                  time_slices).  Classes are not paired; each owns its pixels
+                                  and slices are reduced in a fixed order, so results are
+                                  deterministic.  FP32, one kernel per element; not with
                                   EPIC_JONES (EPIC_ERR_UNSUPPORTED).  Banded channels and
                                   frame mode keep their own launches. */
 

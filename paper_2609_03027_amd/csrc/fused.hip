@@ -190,20 +190,12 @@ __device__ __forceinline__ void gather_load(uint4 (&e)[GB], const uint4 *ent, in
 // The caller loads the first batch (gather_load(e, ent, 0, n_iter)) ahead of
 // the barrier that publishes the staged voltages, so its latency overlaps
 // the wait; later batches are loaded here.
-template <int T, int P, bool JN, int NT = 0>
+template <int T, int P, bool JN>
 __device__ __forceinline__ void gather_cells(Grid<P> grid, const uint4 *ent, int n_iter,
-                                             const float4 *stage, uint4 (&e)[GB],
-                                             const uint4 *tail = nullptr) {
+                                             const float4 *stage, uint4 (&e)[GB]) {
     float2 sx = make_float2(0.f, 0.f), sy = make_float2(0.f, 0.f);
     for (int k0 = 0; k0 < n_iter; k0 += GB) {
-        if (k0 == GB && NT && n_iter <= GB + NT) {
-            // entries GB .. n_iter - 1 are held in registers for the whole
-            // sample loop (they are the same every sample)
-#pragma unroll
-            for (int k = 0; k < GB; ++k) e[k] = k < NT ? tail[k] : e[k];
-        } else if (k0) {
-            gather_load<T, JN>(e, ent, k0, n_iter);
-        }
+        if (k0) gather_load<T, JN>(e, ent, k0, n_iter);
 #pragma unroll
         for (int k = 0; k < GB; ++k) {
             if (k0 + k >= n_iter) break;            // uniform: n_iter is per wave
@@ -1755,7 +1747,8 @@ static epic_status upload_group(epic_plan p, FusedGroup *g, std::vector<FusedIte
 
 // The work queue of an EPIC_BATCH_QUEUE plan: every real item of the size
 // groups, 64 x 64 items first, then same-channel bundles of 32 x 32 and
-// 16 x 16 items (longest processing time first); no time slices.
+// 16 x 16 items, a unit per time slice of its size's group (longest processing
+// time first).
 static epic_status queue_build(epic_plan p, hipStream_t s) {
     // per size: units of one slice; a unit's cost ~ its transform's work x
     // the samples of a slice, so sort by M^2 log M / slices, largest first
