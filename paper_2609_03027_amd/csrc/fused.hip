@@ -1672,6 +1672,14 @@ static epic_status slice_group(epic_plan p, FusedGroup *g, std::vector<FusedItem
     if (slots > 0) {
         // workgroups launched = padded items x slices
         const int64_t wgs = (int64_t)items.size();
+        // beyond 16 slices no more than one round of them (256 elements, 64 channels of
+        // 32^2, 512 samples: 218 us with 32 slices, 184 with the 28 that fit).  Where many
+        // elements leave room for fewer than 16, 16 x 16 items still gain by shorter turns
+        // (2500 elements, 8 channels of 48^2, 50 samples: 666 us with 16, 509 with 57),
+        // 32 x 32 ones, whose start costs more, do not (3000 elements, 8 channels of 96^2:
+        // 508 with 16, 534 with 28).
+        if (S > 16 && (slots >= 16 * wgs || g->M == 32))
+            S = (int)std::max<int64_t>(16, std::min<int64_t>(S, slots / wgs));
         for (int s2 = S; s2 <= 16; ++s2) {
             const double rounds = (double)(wgs * s2) / (double)slots;
             if (rounds / std::ceil(rounds) >= 0.9 || s2 == 16) {
