@@ -338,8 +338,11 @@ __global__ __launch_bounds__(BT) void k_band_cols(const BandChan *__restrict__ c
 // not fit by scattered stores.  Bound by memory: 4096 elements x 2 feeds x 64
 // channels x 128 samples take 29 us, 134 MB read and written.  (Adding the self-term
 // sums here as well costs more than their own pass, which has fewer atomics.)
-constexpr int PKT = 1024;
 constexpr int64_t PK_LDS = 64 << 10;
+// Threads of its workgroups: 1024 while there are few of them (one channel of 16571
+// elements, 50 samples: 20.5 us with 256 threads, 7.0 with 1024), 256 where the chip
+// is full (8192 workgroups: 28 and 38 us).
+constexpr int64_t PK_FEW = 2048;
 // Rounds are packed from these counts on; others read the input, the element of a
 // place by a table.  A pass costs its launch, 1 - 2 us (5000 elements, one 512^2
 // channel, 4 samples: 42.1 us without, 43.3 with), and saves what the scattered bytes
@@ -351,7 +354,7 @@ constexpr int PACK_ELEMENTS = 1000;
 constexpr int64_t PACK_ROUND = 1 << 18;
 
 template <int P, int VB>
-__global__ __launch_bounds__(PKT) void k_band_pack(const uint8_t *__restrict__ volt,
+__global__ __launch_bounds__(1024) void k_band_pack(const uint8_t *__restrict__ volt,
                                                    int64_t vstride,
                                                    const BandChan *__restrict__ chans,
                                                    const int32_t *__restrict__ rank, int A,
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(PKT) void k_band_pack(const uint8_t *__restrict__ v
     uint8_t *dst = out + (int64_t)blockIdx.y * out_t + (int64_t)ci * row;
     Raw *place = reinterpret_cast<Raw *>(lds ? pk_lds : dst);
     if (VB == 1 && (A & 3) == 0 && ((uintptr_t)v & 3) == 0) {      // four elements a load
-        for (int a = 4 * threadIdx.x; a < A; a += 4 * PKT) {
+        for (int a = 4 * (int)threadIdx.x; a < A; a += 4 * (int)blockDim.x) {
             const uint32_t x = *reinterpret_cast<const uint32_t *>(v + a);
             const uint32_t y = P == 2 ? *reinterpret_cast<const uint32_t *>(v + A + a) : 0u;
             const int4 r = *reinterpret_cast<const int4 *>(rank + a);
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(PKT) void k_band_pack(const uint8_t *__restrict__ v
             place[r.w] = (Raw)((x >> 24) | (y >> 24) << 8);
         }
     } else {
-        for (int a = threadIdx.x; a < A; a += PKT) {
+        for (int a = threadIdx.x; a < A; a += (int)blockDim.x) {
             const uint32_t x = volt_raw(v, a, VB);
             const uint32_t y = P == 2 ? volt_raw(v, (int64_t)A + a, VB) : 0u;
             place[rank[a]] = (Raw)(x | y << (8 * (VB & 3)));
@@ -385,7 +388,7 @@ __global__ __launch_bounds__(PKT) void k_band_pack(const uint8_t *__restrict__ v
     __syncthreads();
     // whole 16-byte groups: row is a multiple of 16 and the LDS is as long
     const uint4 *src = reinterpret_cast<const uint4 *>(pk_lds);
-    for (int i = threadIdx.x; i < (int)(row / 16); i += PKT)
+    for (int i = threadIdx.x; i < (int)(row / 16); i += (int)blockDim.x)
         reinterpret_cast<uint4 *>(dst)[i] = src[i];
 }
 
@@ -1593,9 +1596,10 @@ static epic_status launch_pack(epic_plan p, const uint8_t *d_volt, int nt, uint8
     const int use = bp.pack_row <= PK_LDS ? 1 : 0;
     const size_t lds = use ? (size_t)bp.pack_row : 0;
     const dim3 grid((unsigned)bp.n, (unsigned)nt);
+    const unsigned threads = (int64_t)bp.n * nt <= PK_FEW ? 1024u : 256u;
     const int64_t vs = p->vstride(), pt = bp.n * bp.pack_row;
 #define EPIC_PACK(PP, VV)                                                                       \
-    hipLaunchKernelGGL((k_band_pack<PP, VV>), grid, dim3(PKT), lds, s, d_volt, vs,               \
+    hipLaunchKernelGGL((k_band_pack<PP, VV>), grid, dim3(threads), lds, s, d_volt, vs,           \
                        bp.d_chans.as<BandChan>(), bp.d_rank.as<int32_t>(), p->A, packed,        \
                        bp.pack_row, pt, use)
     if (p->P == 2) {

@@ -1,5 +1,6 @@
 """Rounds of the FP32 banded path on both sides of the counts from which their
-voltages are packed (1000 elements; 2^18 elements x channels x samples): element
+voltages are packed (1000 elements; 2^18 elements x channels x samples), and of those from
+which the pack's workgroups are smaller (2048 of them): element
 counts that fill words or not, past what one sample's buffer holds, one and two
 feeds, 4- and 8-bit samples, a packed round followed by one that is not, frames,
 and a captured call."""
@@ -29,6 +30,8 @@ pytestmark = pytest.mark.gpu
     (64, 32772, 2, 4, 4, 512, 0, False),
     (256, 1100, 2, 4, 120, 512, 0, False),
     (512, 2048, 2, 4, 64, 512, 0, False),
+    (64, 1001, 2, 4, 260, 512, 0, False),       # with eight channels: 2080 workgroups
+    (64, 1004, 1, 8, 257, 512, 0, False),
 ])
 def test_rounds(n, n_ant, n_pol, bits, n_time, round_len, frame_len, graph, monkeypatch):
     torch = _torch()
@@ -37,7 +40,7 @@ def test_rounds(n, n_ant, n_pol, bits, n_time, round_len, frame_len, graph, monk
     rng = np.random.default_rng([n, n_ant, n_pol, bits, n_time])
     x = rng.integers(0, n - 2, size=(n_ant, 2)) + 0.5 + rng.uniform(0.0, 0.49, size=(n_ant, 2))
     pos = (x - n / 2.0) * CELL
-    n_chan = 2
+    n_chan = 8 if n == 64 and n_time in (257, 260) else 2
     if bits == 4:
         volt = rng.integers(0, 256, size=(n_time, n_chan, n_pol, n_ant), dtype=np.uint8)
     else:
