@@ -336,7 +336,7 @@ __global__ __launch_bounds__(BT) void k_band_cols(const BandChan *__restrict__ c
 // elements that meet one band lie in a few cache lines.  One workgroup per
 // (sample, channel); the order is applied in LDS, or where a sample's elements do
 // not fit by scattered stores.  Bound by memory: 4096 elements x 2 feeds x 64
-// channels x 128 samples take 29 us, 134 MB read and written.  (Adding the self-term
+// channels x 128 samples take 28 us, 134 MB read and written.  (Adding the self-term
 // sums here as well costs more than their own pass, which has fewer atomics.)
 constexpr int64_t PK_LDS = 64 << 10;
 // Threads of its workgroups: 1024 while there are few of them (one channel of 16571
@@ -541,7 +541,8 @@ __device__ __forceinline__ void pw_load(uint4 (&e)[UN], uint32_t (&bx)[UN],
 // over a slice of samples with its gather list in registers measured slower:
 // the extra registers cost more occupancy than the reuse gained.)
 // Bound by the scratch writes: 6.75 GB (64 channels of 256^2, 128 samples) take
-// 1.25 - 1.45 ms; with the voltages read as scattered bytes they took 1.55 - 1.75.
+// 1.23 - 1.75 ms under the profiler, 1.38 at the median; with the voltages read as
+// scattered bytes 1.55 - 1.75.
 template <int R, int NP, int P, int VB, bool RAW>
 __global__ __launch_bounds__((rows_threads<R, NP>())) void k_band_rows_pw(
     const uint8_t *__restrict__ volt, int64_t volt_t, int64_t pack_row,

@@ -528,9 +528,9 @@ __global__ void k_queue_reset(unsigned int *head) { *head = 0u; }
 //   phase 2: x-pass of sample t + 1 (own rows), staging of sample t + 2.
 // In phase 1 the waves 0-3 (one per SIMD) gather first and the waves 4-7
 // transform first, so that each SIMD has one wave waiting on LDS and one
-// issuing arithmetic.  Bound: vector issue, 1015 instructions per thread and
-// sample on 8 waves and 4 SIMDs (77 % of the cycles; LDS is busy for 46 %).
-// LWA-like station (128 channels, 256 elements), 1000 samples: 4.43 ms (4.6 ms
+// issuing arithmetic.  Bound: vector issue, 1019 instructions per thread and
+// sample on 8 waves and 4 SIMDs (79 % of the cycles; LDS is busy for 47 %).
+// LWA-like station (128 channels, 256 elements), 1000 samples: 4.45 ms (4.6 ms
 // with rows and columns in natural order, see pair_pos).  With
 // workgroup-wide passes (five barriers a sample, both classes' inputs through
 // LDS, 1126 instructions) it took 5.23 ms; 250 samples with Jones kernels 1.27

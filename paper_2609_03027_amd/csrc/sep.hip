@@ -120,9 +120,10 @@ struct SepArgs {
 };
 
 // One workgroup per (time slice, channel, W-column kx tile).  A sample's products
-// keep the matrix cores busy for 3100 clocks of a CU, its vector instructions (the
-// Eq. 2 sums, gather and conversions) the SIMDs for about 3000 and its operands the
-// LDS for 2800; what it takes, 6500, is how far these overlap on two waves a SIMD.
+// keep the matrix cores busy for 3070 clocks of a CU (768 instructions), its other
+// vector instructions (3000: the Eq. 2 sums, gather and conversions) the SIMDs for
+// 3000 and its operands the LDS for 2760 (counters); what it takes, 6840 under the
+// profiler, is how far these overlap on two waves a SIMD.
 // Hence the words of re and im (half the scattered stores and step-1 reads), the
 // two waves of a SIMD at different phases and the products' higher priority:
 // 128 channels of 256 elements, 250 samples, took 1055 us before and 845 us now

@@ -365,8 +365,8 @@ __global__ __launch_bounds__(1024) void k_fft2d(const float2 *in, float2 *out,
 // flight during the remaining steps.  Rows of one LDS image lie N + 1 apart.
 //
 // Bound: HBM (one read and one write per image).  64 samples of 32 channels of
-// 128^2 with two feeds, 1.07 GB: 226 us (4.7 TB/s, the rate of a
-// device copy) against 341 with radix-4 passes
+// 128^2 with two feeds, 1.07 GB: 230 us (4.7 TB/s, the rate of a
+// device copy; the same with the twiddles in the butterflies) against 341 with radix-4 passes
 // through LDS (eight passes, seventeen barriers, a quarter of the next image
 // in flight).
 template <int N> struct P2Cfg;
